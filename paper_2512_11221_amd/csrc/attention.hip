@@ -1,64 +1,78 @@
-// Active-set GQA flash-decode for gfx950, fused with the relevance score, and
-// the per-layer split combine.
+// Active-set GQA flash-decode for gfx950, fused with the relevance products
+// and the split combine.
 //
 // Per launch (one layer, every sequence):
 //   Eq. 1  o_h = softmax_j(q_h . k_j / sqrt(D)) v_j over the active list A_t;
-//   Eq. 2  s_j = (1/Hq) sum_h |q_h . k_j| for every j in A_t, and the flag
-//          s_j < tau stored per position; Algorithm 1's freeze loop reads the
-//          flags at the end of the step (in the list rebuild, which streams
-//          every position's state anyway), so no count or unfreeze step is
-//          read or written here.
+//   Eq. 2  the relevance of every j in A_t: per KV head the sum over its
+//          query heads of |q_h . k_j| (or, for the reading by attention
+//          weight, the logit of every query head), one value per list entry
+//          and plane.  The end-of-step verdict sums the planes and compares
+//          with tau, so no score crosses workgroups here.
 //
-// Work decomposition.  The active lists of all sequences, concatenated (each
-// preceded by a few virtual tokens that stand for the fixed cost of a
-// sequence), are cut into equal contiguous ranges, one per workgroup of a
-// fixed grid, computed on the device from the active counts.  Inside a
-// workgroup the range is walked in tiles dealt round-robin to its waves (a
-// static deal, so every run sums in the same order); a wave that falls
-// behind the others raises its issue priority until it has caught up.  The
-// waves' softmax states are merged through LDS once per sequence the range
-// touches, giving one partial (m, l, acc) of every query head at slot
-// (workgroup + sequence): when all eight states fit in LDS each wave folds
-// them for a slice of the rows in one round, otherwise a three-round tree
-// folds pairs.
+// Work decomposition.  The cache is head-major, so a (sequence, KV head) pair
+// is one stream of contiguous rows: its active list, cut into tiles of 32
+// tokens, is a list of tiles.  The tile lists of all pairs, concatenated (each
+// preceded by a few virtual tiles that stand for the fixed cost of a piece),
+// are cut into equal contiguous ranges, one per workgroup of a fixed grid,
+// computed on the device from the active counts.  A pair with one workgroup is
+// finished by it; a pair shared by several leaves one partial (m, l, acc) per
+// workgroup, and the workgroup that arrives last (a per-pair ticket) folds
+// them in slot order and writes the outputs.  A partial holds one KV head's
+// query heads only, so the last one pulls a few KB; with whole-row workgroups
+// (every KV head of a token range) it would be the sequence's half megabyte,
+// which took a launch of its own.
 //
-// Lane layout inside a wave: 8 slots x 8 lanes.  Slot s holds KV head
-// s % Hkv of token s / Hkv of the iteration (8 / Hkv tokens per iteration),
-// so a wave reads whole token rows (every KV head) and every load
-// instruction moves 8 contiguous 128-byte segments.  A slot's row serves the
-// G query heads of its KV head from registers (GQA sharing); dot products are
-// reduced over the slot's 8 lanes with DPP, the relevance over the token's
-// KV-head slots with lane exchanges, so the score flag is decided in the
-// wave and stored by the workgroup after each chunk.
+// Why head-major: a plain streaming kernel of this grid moves dense ranges at
+// 6.99 TB/s and 35 % gathers at 6.75 TB/s when a wave's load instruction covers
+// four whole 256-byte head rows of a head-major cache; 6.82 and 6.52 TB/s for
+// whole 2 KiB rows of a token-major cache, 6.29 and 5.85 TB/s for 256-byte rows
+// of a token-major cache, and 5.98 and 5.41 TB/s for 64-byte pieces of 16 rows
+// (the lane layout of the matrix instruction, hence the LDS tiles below).
 //
-// Wide groups and many KV heads.  With G = 8 a slot holds a virtual KV head,
-// one KV head with half of its query heads (two slots read the same row, in
-// the same load instruction).  When a token has more than 8 (virtual) heads,
-// 2 or 4 waves share each token, each with 8 of them; their parts of the
-// relevance sum meet in LDS after the tiles, where the flag is decided.
+// Inside a workgroup every wave takes whole tiles (round-robin, a static deal,
+// so every run sums in the same order).  A tile's K and V rows travel through
+// registers into the wave's own LDS tile, the next tile's rows are requested
+// at once, and the arithmetic runs on the matrix cores from LDS: no barrier in
+// the loop.  Scores: S^T = K Q^T with the tokens as rows, the query heads
+// (repeated) as the 16 columns.  Accumulate: O += P V with P's rows the heads;
+// the column layout of S^T is the row layout of P, so the weights stay in their
+// lanes.  fp32 rows use the fp32 matrix instruction.  bf16 rows keep fp32
+// weights: the repeated columns carry p's leading, middle and trailing 8
+// mantissa bits as three bf16 rows (exact: p = hi + mid + lo), summed in fp32
+// when the waves are merged.
+#include <type_traits>
+
 #include "kernels.h"
 
 namespace asrkf {
 namespace {
 
-constexpr int kWaves = 8;           // waves per workgroup
-constexpr int kChunk = 2048;        // tokens per LDS chunk (positions, score flags)
-constexpr int kMinPerGroup = 32;    // fewest tokens worth a workgroup
-// Each sequence a workgroup takes part in costs it a fixed set-up and merge
-// (list staging, q, the freeze loop, the wave-state merge, a partial), about
-// what streaming this many tokens takes; the planner charges it as virtual
-// tokens ahead of every non-empty list, so a workgroup whose range straddles
-// two sequences gets correspondingly fewer real tokens.
-constexpr int kSeqCost = 48;
-constexpr int kStage = kChunk / (64 * kWaves);   // chunk entries per thread
+// What a piece costs a workgroup beside its rows (set-up round trips, merge,
+// partial), in tiles of one KV head streamed: about 6 us against 0.6 us a tile.
+constexpr int kPieceCost = 10;
+// Fewest tiles of one KV head worth a workgroup, and the share up to which only
+// half of the workgroups are used: with little work the launch is bound by fixed
+// latencies, and 256 workgroups start two microseconds later than 128 (one
+// sequence of 4093 tokens, 8 KV heads: 14.4 us with 128 workgroups of 8 tiles,
+// 15.4 with 256 of 4; of 1500 tokens: 11.9 with 96 of 4, 13.2 with 48 of 8).
+constexpr int kMinTiles = 4;
+constexpr int kHalfTiles = 8;
 // raw buffer descriptor word 3 for gfx9-class targets (32-bit data, no swizzle)
 constexpr int kBufferFlags = 0x00020000;
 // cache policy of the K/V row loads: non-temporal.  Each row is read once per
-// launch, so the loads should not displace anything in L2 / MALL; on gfx950
-// this raised the streaming rate of this kernel by about a tenth.
+// launch; the streaming probe above reaches 6.07 and 5.83 TB/s without it.
 constexpr int kStreamPolicy = 2;
+// cache policy of the partials that workgroups exchange: device scope (past the
+// XCD's own L2)
+constexpr int kAgentScope = 16;
+// an offset past every buffer's range (a pair's rows stay below 2 GiB): loads
+// there return zeros and stores are dropped, without a memory access, so
+// masked lanes cost nothing and the compiler counts every wait exactly
+constexpr int kNowhere = (int)0x80000000;
+// a wave rescales its sums when a score passes the running maximum by more
+// than this (log2 units): weights stay below 2^6, far from any fp32 limit
+constexpr float kMaxLag = 6.f;
 
-// A value the whole wave agrees on, moved to a scalar register.
 __device__ __forceinline__ int wave_uniform(int x) { return __builtin_amdgcn_readfirstlane(x); }
 
 template <int CTRL>
@@ -66,892 +80,883 @@ __device__ __forceinline__ float dpp_mov(float v) {
     return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xF, 0xF, false));
 }
 
-// value of lane (lane ^ mask) for mask in {8, 16, 32}
-template <int MASK>
-__device__ __forceinline__ float lane_xor(float v) {
-    if constexpr (MASK == 8) return dpp_mov<0x128>(v);    // row_ror:8
-    else return __shfl_xor(v, MASK);
+// value of lane N of the lane's row of 16
+template <int N>
+__device__ __forceinline__ int row_bcast(int v) {
+    return __builtin_amdgcn_update_dpp(0, v, 0x150 + N, 0xF, 0xF, false);
 }
 
-__device__ __forceinline__ float bf16_lo(uint32_t w) { return __uint_as_float(w << 16); }
-__device__ __forceinline__ float bf16_hi(uint32_t w) { return __uint_as_float(w & 0xFFFF0000u); }
-
-typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
-
-__device__ __forceinline__ float dot2_bf16(uint32_t a, uint32_t b, float c) {
-    return __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2_t, a),
-                                           __builtin_bit_cast(bf16x2_t, b), c, false);
+template <int N, typename F>
+__device__ __forceinline__ void unroll(F f) {
+    if constexpr (N > 0) {
+        unroll<N - 1>(f);
+        f(std::integral_constant<int, N - 1>{});
+    }
 }
+
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef float floatx4 __attribute__((ext_vector_type(4)));
+typedef int intx2 __attribute__((ext_vector_type(2)));
+typedef int intx4 __attribute__((ext_vector_type(4)));
+typedef float floatx2 __attribute__((ext_vector_type(2)));
+typedef unsigned uintx2 __attribute__((ext_vector_type(2)));
+typedef unsigned uintx4 __attribute__((ext_vector_type(4)));
+typedef short shortx4 __attribute__((ext_vector_type(4)));
+typedef __attribute__((address_space(3))) shortx4* lds_shortx4;
+
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t buffer(const void* p, int bytes) {
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), (short)0, bytes, kBufferFlags);
+}
+
+template <int POLICY>
+__device__ __forceinline__ intx4 load16(__amdgpu_buffer_rsrc_t r, int off) {
+    return __builtin_bit_cast(intx4, __builtin_amdgcn_raw_buffer_load_b128(r, off, 0, POLICY));
+}
+
+// A barrier for what the waves share in LDS.  __syncthreads also waits for every
+// load and store in flight: the next tile's rows, the relevance stores and the
+// append, which nobody in the workgroup reads back.
+__device__ __forceinline__ void lds_barrier() {
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+}
+
+// ---- the split ----
+//
+// Tiles of the (sequence, head group) pairs dealt to the workgroups, from the
+// active counts.  Two forms, chosen by what the longest share would be:
+//  aligned   every pair is cut into parts of at most `share` tiles, one
+//            workgroup each (a workgroup never takes a second piece, which
+//            would cost it set-up, merge and partial again);
+//  straddled the pairs' tile lists, each preceded by `cost` virtual tiles, are
+//            concatenated and cut into equal ranges: when the lengths differ so
+//            much, or the pairs are so many, that aligned parts would leave some
+//            workgroup more than a piece's cost above the average.
+// Batches of up to 64 sequences are planned by every wave for itself, one
+// sequence per lane, without a barrier; larger ones by wave 0 into LDS.
+struct Plan {
+    int tile;                       // tokens per tile
+    int groups, cost, limit;        // head groups per sequence, piece cost in tiles, workgroups
+    bool aligned;
+    int share;                      // aligned: tiles per part; straddled: tiles per range (the first
+    int extra;                      //   `extra` ranges have one more)
+    int live;                       // workgroups with work
+    // sequence b owns units [off, off + units): workgroups (aligned) or tiles (straddled)
+    int n, units, off;              // of the lane's sequence (up to 64 sequences)
+    const int32_t* lds;             // [B + 1] offsets, then [B] counts (more than 64)
+    int B;
+
+    __device__ __forceinline__ int parts(int tiles) const { return (tiles + share - 1) / share; }
+    __device__ __forceinline__ int tiles_of(int n) const { return (n + tile - 1) / tile; }
+    __device__ __forceinline__ int units_of(int n) const {
+        const int tiles = tiles_of(n);
+        return n == 0 ? 0 : groups * (aligned ? parts(tiles) : tiles + cost);
+    }
+    // total: tiles of all sequences, longest: of the longest, filled: sequences with any
+    __device__ __forceinline__ void choose(int total, int longest, int filled) {
+        const int average = (total * groups + limit - 1) / limit;
+        const int most = limit / max(1, filled * groups);         // parts a pair can have
+        share = max(kMinTiles / min(kMinTiles, limit_heads), most > 0 ? (longest + most - 1) / most : 0);
+        share = max(share, min(kHalfTiles / min(kHalfTiles, limit_heads), 2 * average));
+        aligned = most > 0 && share <= max(average + cost, kHalfTiles);
+    }
+    int limit_heads;                // KV heads a workgroup takes together
+    __device__ __forceinline__ void ranges(int T) {               // straddled, after the scan
+        live = max(1, min(limit, T / kMinTiles));
+        share = T / live;
+        extra = T - share * live;
+        if (T == 0) live = 0;
+    }
+    __device__ __forceinline__ int start(int w) const { return w * share + min(w, extra); }
+    __device__ __forceinline__ int owner(int x) const {           // the range holding tile x
+        const int head = extra * (share + 1);
+        return x < head ? x / (share + 1) : extra + (x - head) / share;
+    }
+    // the sequence that owns unit x
+    __device__ __forceinline__ int find(int x) const {
+        if (B <= 64) return __popcll(__ballot((int)(threadIdx.x & 63) < B && off + units <= x));
+        int l0 = 0, h0 = B - 1;                                   // last b with lds[b] <= x
+        while (l0 < h0) {
+            const int mid = (l0 + h0 + 1) >> 1;
+            if (wave_uniform(lds[mid]) <= x) l0 = mid; else h0 = mid - 1;
+        }
+        while (wave_uniform(lds[l0 + 1]) <= x) ++l0;              // past empty lists
+        return l0;
+    }
+    __device__ __forceinline__ void range(int w, int& x, int& x_end) const {
+        x = aligned ? w : start(w);
+        x_end = aligned ? w + 1 : start(w + 1);
+    }
+    // The workgroup of index i takes range w: workgroups are dealt to the 8 XCDs
+    // round robin, and when every workgroup has work each XCD takes a contiguous
+    // block of ranges.  Any one-to-one map gives the same partials.
+    __device__ __forceinline__ int range_of(int i) const {
+        return live == limit && limit % 8 == 0 ? (i % 8) * (limit / 8) + i / 8 : i;
+    }
+    __device__ __forceinline__ int offset(int b) const {
+        return B <= 64 ? __builtin_amdgcn_readlane(off, b) : wave_uniform(lds[b]);
+    }
+    __device__ __forceinline__ int count(int b) const {
+        return B <= 64 ? __builtin_amdgcn_readlane(n, b) : wave_uniform(lds[B + 1 + b]);
+    }
+};
+
+// One workgroup's part of a pair.
+struct Piece {
+    int b, n;                       // sequence, its active count
+    int group;                      // head group
+    int t0, t1;                     // tiles
+    int n_parts, part, slot;        // workgroups sharing the pair, which of them, partial slot
+};
+
+// The next piece of range w from unit x on (x moves past it); false: only
+// virtual tiles were left.
+__device__ __forceinline__ bool next_piece(const Plan& plan, int w, int& x, int x_end, Piece& p) {
+    while (x < x_end) {
+        p.b = plan.find(x);
+        const int so = plan.offset(p.b);
+        p.n = plan.count(p.b);
+        const int tiles = plan.tiles_of(p.n);
+        if (plan.aligned) {
+            p.n_parts = plan.parts(tiles);
+            p.group = (x - so) / p.n_parts;
+            p.part = x - so - p.group * p.n_parts;
+            p.t0 = p.part * plan.share;
+            p.t1 = min(tiles, p.t0 + plan.share);
+            p.slot = x;
+            ++x;
+            return true;
+        }
+        const int units = tiles + plan.cost;      // of one head group
+        p.group = (x - so) / units;
+        const int first = so + p.group * units + plan.cost;       // the pair's first tile
+        const int end = min(first + tiles, x_end);
+        const int from = max(x, first);
+        x = end;
+        if (end <= first) continue;               // virtual tiles only
+        p.t0 = from - first;
+        p.t1 = end - first;
+        const int w0 = plan.owner(first);
+        p.n_parts = plan.owner(first + tiles - 1) - w0 + 1;
+        p.part = w - w0;
+        p.slot = w + p.b * plan.groups + p.group;
+        return true;
+    }
+    return false;
+}
+
+struct PlanInput {
+    const int32_t* n_active;
+    int B, Hkv, heads_per_group, grid;
+};
+
+__device__ __forceinline__ Plan make_plan(const PlanInput& a, int tile, int32_t* lds) {
+    Plan p;
+    p.tile = tile;
+    p.groups = a.Hkv / a.heads_per_group;
+    p.cost = max(1, kPieceCost / a.heads_per_group);
+    p.limit = a.grid;
+    p.limit_heads = a.heads_per_group;
+    p.B = a.B;
+    p.lds = lds;
+    const int lane = threadIdx.x & 63;
+    int total = 0;
+    if (a.B <= 64) {
+        p.n = lane < a.B ? a.n_active[lane] : 0;
+        const int tiles = p.tiles_of(p.n);
+        int sum = tiles, top = tiles;
+        if (a.B > 1) {
+            for (int o = 1; o < a.B; o <<= 1) {                   // lanes past B hold 0
+                sum += __shfl_xor(sum, o);
+                top = max(top, __shfl_xor(top, o));
+            }
+        }
+        const int filled = __popcll(__ballot(p.n > 0));
+        p.choose(wave_uniform(sum), wave_uniform(top), filled);
+        p.units = p.units_of(p.n);
+        int incl = p.units;
+        if (a.B > 1) {
+            for (int o = 1; o < a.B; o <<= 1) {
+                const int y = __shfl_up(incl, o);
+                if (lane >= o) incl += y;
+            }
+        }
+        p.off = incl - p.units;
+        total = __builtin_amdgcn_readlane(incl, a.B - 1);
+    } else {
+        int32_t* off = lds;
+        int32_t* cnt = lds + a.B + 1;
+        __shared__ int summary[3];
+        if (threadIdx.x < 64) {
+            constexpr int kBatch = 8;                 // counts loaded together
+            const int per = (a.B + 63) / 64;
+            const int b0 = min(a.B, lane * per), b1 = min(a.B, b0 + per);
+            int sum = 0, top = 0, filled = 0;
+            for (int bb = b0; bb < b1; bb += kBatch) {
+                int c[kBatch];
+#pragma unroll
+                for (int k = 0; k < kBatch; ++k) c[k] = a.n_active[min(bb + k, b1 - 1)];
+#pragma unroll
+                for (int k = 0; k < kBatch; ++k) {
+                    if (bb + k >= b1) continue;
+                    cnt[bb + k] = c[k];
+                    const int tiles = p.tiles_of(c[k]);
+                    sum += tiles;
+                    top = max(top, tiles);
+                    filled += c[k] > 0;
+                }
+            }
+            for (int o = 1; o < 64; o <<= 1) {
+                sum += __shfl_xor(sum, o);
+                top = max(top, __shfl_xor(top, o));
+                filled += __shfl_xor(filled, o);
+            }
+            p.choose(wave_uniform(sum), wave_uniform(top), wave_uniform(filled));
+            int mine = 0;
+            for (int bb = b0; bb < b1; ++bb) mine += p.units_of(cnt[bb]);
+            int incl = mine;
+            for (int o = 1; o < 64; o <<= 1) {
+                const int y = __shfl_up(incl, o);
+                if (lane >= o) incl += y;
+            }
+            int run = incl - mine;
+            for (int bb = b0; bb < b1; ++bb) {
+                off[bb] = run;
+                run += p.units_of(cnt[bb]);
+            }
+            if (lane == 63) {
+                off[a.B] = incl;
+                summary[0] = p.share;
+                summary[1] = p.aligned ? 1 : 0;
+            }
+        }
+        __syncthreads();
+        p.share = wave_uniform(summary[0]);
+        p.aligned = wave_uniform(summary[1]) != 0;
+        total = wave_uniform(off[a.B]);
+    }
+    p.extra = 0;
+    if (p.aligned) p.live = total;
+    else p.ranges(total);
+    return p;
+}
+
+// ---- tiles ----
 
 template <bool BF16, int D>
 struct Row {
     static constexpr int kElem = BF16 ? 2 : 4;
-    static constexpr int kBytes = D * kElem;       // one token, one KV head
-    static constexpr int kChunks = kBytes / 128;   // 16-byte pieces per lane
-    static constexpr int kPerChunk = 16 / kElem;
-    static constexpr int kPerLane = kChunks * kPerChunk;  // = D / 8
+    static constexpr int kBytes = D * kElem;              // one token, one KV head
+    static constexpr int kLanes = kBytes / 16;            // lanes per row in a load
+    // tokens per tile: 16 KB of K and V rows, in a wave's registers while they travel
+    static constexpr int kTile = 8192 / kBytes;
+    static constexpr int kBlocks = kTile / 16;            // score blocks of 16 tokens
+    static constexpr int kLoads = kTile * kLanes / 64;    // load instructions per tile (K or V)
+    // LDS row strides: the padding shifts consecutive rows by 4 (K) and 8 (V)
+    // banks, so the 16-byte reads of K rows and the transposed reads of V rows
+    // meet no bank twice.  A wave's K tile is read before its V tile is written,
+    // in the same place.
+    static constexpr int kKStride = kBytes + 16;
+    static constexpr int kVStride = kBytes + 32;
+    static constexpr int kTileLds = kTile * kVStride;
+    // room for the relevance values a wave keeps before they are stored
+    static constexpr int kRelLds = 8192;
+    static constexpr int kWaveLds = kTileLds + kRelLds;
+    static constexpr int kWaves = 8;
+    static constexpr int kQRegs = BF16 ? D / 32 : D / 16; // 16-byte pieces of q per lane
 };
 
-// Iterations per tile: four, or two when a lane holds four pieces of a row
-// (bf16 rows of 256, fp32 rows of 128), so that a tile's rows stay in registers.
-template <bool BF16, int D>
-constexpr int tile_unroll() { return Row<BF16, D>::kChunks >= 4 ? 2 : 4; }
+// Rows of P: query head h of part p sits in row p * G + h.  With G = 8 the
+// sixteen rows hold two parts, the third is accumulated apart.
+template <bool BF16, int G>
+constexpr int parts_apart() { return BF16 && G == 8 ? 1 : 0; }
 
-template <bool BF16, int D>
-using Pieces = uint4[Row<BF16, D>::kChunks];      // the lane's 16-byte pieces of a row
-template <bool BF16, int D>
-using LaneAcc = float[Row<BF16, D>::kPerLane];    // the lane's accumulators of one head
-
-// Dot product of the lane's part of a row with the lane's part of q.
-template <bool BF16, int D>
-__device__ __forceinline__ float lane_dot(const Pieces<BF16, D>& k, const Pieces<BF16, D>& q) {
-    float x = 0.f;
+// (L, o) += wgt * (l, v)
+__device__ __forceinline__ void fold(float& L, floatx4& o, float wgt, float l, floatx4 v) {
+    L = fmaf(wgt, l, L);
 #pragma unroll
-    for (int c = 0; c < Row<BF16, D>::kChunks; ++c) {
-        if constexpr (BF16) {
-            x = dot2_bf16(k[c].x, q[c].x, x);
-            x = dot2_bf16(k[c].y, q[c].y, x);
-            x = dot2_bf16(k[c].z, q[c].z, x);
-            x = dot2_bf16(k[c].w, q[c].w, x);
-        } else {
-            x = fmaf(__uint_as_float(k[c].x), __uint_as_float(q[c].x), x);
-            x = fmaf(__uint_as_float(k[c].y), __uint_as_float(q[c].y), x);
-            x = fmaf(__uint_as_float(k[c].z), __uint_as_float(q[c].z), x);
-            x = fmaf(__uint_as_float(k[c].w), __uint_as_float(q[c].w), x);
+    for (int i = 0; i < 4; ++i) o[i] = fmaf(wgt, v[i], o[i]);
+}
+
+// Where a piece's outputs go.
+struct Finish {
+    float* out;                     // first query head of the piece
+    float* norm;                    // its normaliser, or null
+    template <int D>
+    __device__ __forceinline__ void write(int hh, int d, float M, float L, floatx4 o) const {
+        floatx4 r;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) r[i] = o[i] / L;
+        *reinterpret_cast<floatx4*>(out + (size_t)hh * D + d) = r;
+        if (norm && d == 0) {
+            norm[hh * 2] = M;
+            norm[hh * 2 + 1] = L;
         }
     }
-    return x;
-}
-
-// acc[e] += p * v[e] over the lane's elements.
-template <bool BF16, int D>
-__device__ __forceinline__ void lane_axpy(LaneAcc<BF16, D>& acc, float p, const Pieces<BF16, D>& v) {
-#pragma unroll
-    for (int c = 0; c < Row<BF16, D>::kChunks; ++c) {
-        const uint32_t w[4] = {v[c].x, v[c].y, v[c].z, v[c].w};
-        if constexpr (BF16) {
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                acc[c * 8 + 2 * i] = fmaf(p, bf16_lo(w[i]), acc[c * 8 + 2 * i]);
-                acc[c * 8 + 2 * i + 1] = fmaf(p, bf16_hi(w[i]), acc[c * 8 + 2 * i + 1]);
-            }
-        } else {
-#pragma unroll
-            for (int i = 0; i < 4; ++i) acc[c * 4 + i] = fmaf(p, __uint_as_float(w[i]), acc[c * 4 + i]);
-        }
-    }
-}
-
-// Offsets of every sequence in the concatenated, cost-padded active lists:
-// sequence b owns [seq_off[b], seq_off[b+1]), whose first kSeqCost entries
-// are virtual (none for an empty list); seq_off[B] = T.  Wave 0 scans.
-__device__ void plan_ranges(const int32_t* n_active, int B, int32_t* seq_off) {
-    const int tid = threadIdx.x;
-    if (tid < 64) {
-        constexpr int kBatch = 8;                 // counts loaded together
-        const int per = (B + 63) / 64;
-        const int b0 = tid * per;
-        const int b1 = min(B, b0 + per);
-        int mine = 0;
-        for (int bb = b0; bb < b1; bb += kBatch) {
-            int cost[kBatch];
-#pragma unroll
-            for (int k = 0; k < kBatch; ++k) {
-                const int n = bb + k < b1 ? n_active[bb + k] : 0;
-                cost[k] = n > 0 ? n + kSeqCost : 0;
-            }
-#pragma unroll
-            for (int k = 0; k < kBatch; ++k) {
-                if (bb + k < b1) seq_off[bb + k] = cost[k];      // kept here until the scan is done
-                mine += cost[k];
-            }
-        }
-        int incl = mine;
-        for (int o = 1; o < 64; o <<= 1) {
-            const int y = __shfl_up(incl, o);
-            if (tid >= o) incl += y;
-        }
-        int run = incl - mine;
-        for (int bb = b0; bb < b1; ++bb) {
-            const int c = seq_off[bb];
-            seq_off[bb] = run;
-            run += c;
-        }
-        if (tid == 63) seq_off[B] = incl;
-    }
-}
-
-// Workgroups that share the tokens: enough that each gets kMinPerGroup of them.
-__device__ __forceinline__ int active_groups(int T, int grid) {
-    return max(1, min(grid, (T + kMinPerGroup - 1) / kMinPerGroup));
-}
-
-// Workgroup holding token x when T tokens are cut into G ranges
-// [floor(w T / G), floor((w+1) T / G)).
-__device__ __forceinline__ int group_of(int64_t x, int64_t T, int64_t G) {
-    return (int)(((x + 1) * G - 1) / T);
-}
-
-// Online-softmax state of one lane: its slot's G query heads.
-template <bool BF16, int D, int G>
-struct SoftState {
-    float m[G], l[G];
-    float acc[G][Row<BF16, D>::kPerLane];
 };
 
-// Fold state b into state a (both of the same lane), fixed order.
-template <bool BF16, int D, int G>
-__device__ __forceinline__ void fold(SoftState<BF16, D, G>& a, const float* bm, const float* bl,
-                                     const float (*bacc)[Row<BF16, D>::kPerLane]) {
+// a finite value as it is, anything else 0
+__device__ __forceinline__ float finite_or_0(float x) { return fabsf(x) < INFINITY ? x : 0.f; }
+
+// a's rows 1, 3 (of 16 lanes) exchanged with b's rows 0, 2, then added:
+// rows a0 + a1, b0 + b1, a2 + a3, b2 + b3
+__device__ __forceinline__ float add_rows16(float a, float b) {
+    const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+    return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
+// a's upper half exchanged with b's lower half, then added: rows a0 + a2, a1 + a3, b0 + b2, b1 + b3
+__device__ __forceinline__ float add_halves(float a, float b) {
+    const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+    return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
+
+// A wave's accumulators as [G][kMergeStride] sums in LDS.  Row 4 q4 + i, column
+// c16 of block k; the parts of a bf16 weight are added here.  Where a value row
+// holds an infinity, the leading part has the result and the others may hold
+// 0 * inf, so those count only while they are finite.
+template <bool BF16, int D, int G, typename Acc, typename Acc2>
+__device__ __forceinline__ void store_state(const Acc& acc, const Acc2& acc2, float* st, int lane) {
+    constexpr int S = D + 4;
+    const int c16 = lane & 15, q4 = lane >> 4;
 #pragma unroll
-    for (int h = 0; h < G; ++h) {
-        const float M = fmaxf(a.m[h], bm[h]);
-        const float sa = (a.m[h] == -INFINITY) ? 0.f : __builtin_amdgcn_exp2f(a.m[h] - M);
-        const float sb = (bm[h] == -INFINITY) ? 0.f : __builtin_amdgcn_exp2f(bm[h] - M);
-        a.l[h] = a.l[h] * sa + bl[h] * sb;
+    for (int k = 0; k < D / 16; ++k) {
+        float* col = st + k * 16 + c16;
+        const floatx4 v = acc[k];
+        if constexpr (!BF16) {
 #pragma unroll
-        for (int e = 0; e < Row<BF16, D>::kPerLane; ++e) a.acc[h][e] = a.acc[h][e] * sa + bacc[h][e] * sb;
-        a.m[h] = M;
+            for (int i = 0; i < (G < 4 ? G : 4); ++i)
+                if (q4 * 4 < G) col[(q4 * 4 + i) * S] = v[i];
+        } else if constexpr (G == 1) {
+            const float x = v[0] + (finite_or_0(v[1]) + finite_or_0(v[2]));
+            if (q4 == 0) col[0] = x;
+        } else if constexpr (G == 2) {
+            const float x0 = q4 == 0 ? v[0] + finite_or_0(v[2]) : finite_or_0(v[0]);
+            const float x1 = q4 == 0 ? v[1] + finite_or_0(v[3]) : finite_or_0(v[1]);
+            const float x = add_rows16(x0, x1);
+            if (q4 < 2) col[q4 * S] = x;
+        } else if constexpr (G == 4) {
+            float x[4];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) x[i] = q4 == 0 ? v[i] : q4 < 3 ? finite_or_0(v[i]) : 0.f;
+            col[q4 * S] = add_halves(add_rows16(x[0], x[1]), add_rows16(x[2], x[3]));
+        } else {
+            const int h = (q4 & 1) * 4 + (q4 >> 1);
+#pragma unroll
+            for (int i = 0; i < 4; i += 2) {
+                const float x0 = q4 < 2 ? v[i] : finite_or_0(v[i]);
+                const float x1 = q4 < 2 ? v[i + 1] : finite_or_0(v[i + 1]);
+                const float lo = finite_or_0(q4 < 2 ? acc2[k][i] : acc2[k][i + 1]);
+                col[(h + i) * S] = add_halves(x0, x1) + lo;
+            }
+        }
     }
 }
 
-// How many parts a KV head's query heads are split into, so that a lane keeps
-// the softmax state of at most four heads (two for rows of 256): the state of
-// more does not fit in a wave's registers.
+template <bool BF16, int D>
+constexpr int threads_of() { return 64 * Row<BF16, D>::kWaves; }
+
 template <bool BF16, int D, int G>
-constexpr int split_of() {
-    constexpr int kMaxHeads = Row<BF16, D>::kPerLane >= 32 ? 2 : 4;
-    return G > kMaxHeads ? G / kMaxHeads : 1;
-}
-
-// Shapes the kernel handles: a token row (every KV head) goes into the cache
-// with one 16-byte piece per thread, and after the split no more waves share a
-// token than there are waves per state part to fold a head's rows.
-template <bool BF16, int D, int G, int HKV>
-constexpr bool shape_supported() {
-    constexpr int GS = G / split_of<BF16, D, G>();
-    constexpr int VH = HKV * split_of<BF16, D, G>();
-    constexpr int NWG = VH > 8 ? VH / 8 : 1;
-    return (D != 256 || BF16) && HKV * Row<BF16, D>::kBytes <= 64 * kWaves * 16 && NWG <= 4 &&
-           GS <= kWaves / NWG;
-}
-
-// All 8 wave states fit in LDS next to the other buffers: merge in one round.
-template <bool BF16, int D, int G>
-constexpr bool merge_one_round() {
-    return (size_t)kWaves * (2 * G + G * Row<BF16, D>::kPerLane) * 64 * 4 <= 148 * 1024;
-}
-
-// Shapes whose first tile can come from the plan records: one token per wave
-// iteration, one wave per token, the first tiles of all waves within the
-// record's positions.
-template <bool BF16, int D, int G, int HKV>
-constexpr bool prefetch_shape() {
-    constexpr int VH = HKV * split_of<BF16, D, G>();
-    constexpr int NWG = VH > 8 ? VH / 8 : 1;
-    constexpr int TPI = 8 / (VH > 8 ? 8 : VH);
-    return TPI == 1 && NWG == 1 && kWaves * tile_unroll<BF16, D>() <= kPlanTokens;
-}
-
-// PF: the first tile of a range's first chunk is requested from the plan
-// record (a.plan must be set); without it the kernel never reads a.plan.
-template <bool BF16, int D, int G, int HKV, bool PF>
-__global__ void __launch_bounds__(64 * kWaves)
+__global__ void __launch_bounds__((threads_of<BF16, D>()), 2)
 attention_kernel(AttnArgs a) {
     using R = Row<BF16, D>;
-    // Wide query groups (G = 8) are split in halves of GS heads: a lane keeps the
-    // softmax state of GS query heads only, so it fits in registers.  A virtual
-    // KV head is a (KV head, half) pair, VH of them.  When a token has more
-    // virtual heads than a wave has slots, NWG waves share each token (wave
-    // part p takes virtual heads 8p .. 8p + 7) and the relevance of the parts is
-    // summed in LDS after the tiles.
-    constexpr int kSplit = split_of<BF16, D, G>();
-    constexpr int kUnroll = tile_unroll<BF16, D>();
-    constexpr int GS = G / kSplit;               // query heads per lane
-    constexpr int VH = HKV * kSplit;             // virtual KV heads
-    constexpr int NWG = VH > 8 ? VH / 8 : 1;     // waves sharing a token
-    constexpr int SV = VH > 8 ? 8 : VH;          // virtual heads of a token in one wave
-    constexpr int kGroups = kWaves / NWG;        // tiles are dealt to groups of NWG waves
-    using S = SoftState<BF16, D, GS>;
-    constexpr int NC = R::kChunks;
-    constexpr int EL = R::kPerLane;
-    constexpr int TPI = 8 / SV;                  // tokens per iteration
-    constexpr int TT = kUnroll * TPI;            // tokens per tile
-    constexpr int NV = 2 * GS + GS * EL;         // floats of a lane's state
-    constexpr bool kOneRound = merge_one_round<BF16, D, GS>();
-    static_assert(shape_supported<BF16, D, G, HKV>(), "unsupported head layout");
+    constexpr int kWaves = R::kWaves;
+    constexpr int kThreads = threads_of<BF16, D>();
+    constexpr int kTile = R::kTile;
+    constexpr int NBLK = R::kBlocks;
+    constexpr int NL = R::kLoads;
+    constexpr int NQ = R::kQRegs;
+    constexpr int NB = D / 16;                    // column blocks of the accumulators
+    constexpr int kApart = parts_apart<BF16, G>();
+    static_assert(G * (D + 4) * 4 <= R::kTileLds, "wave state fits its tile");
+    static_assert(64 * 24 <= R::kTileLds, "a wave's folded states fit its tile");
 
-    extern __shared__ int32_t lds[];
-    __shared__ unsigned tile_lead;                               // most tiles any wave has finished
-    int32_t* seq_off = lds;                                      // [B + 1]
-    int32_t* pos_lds = lds + ((a.B + 1 + 3) & ~3);               // [kChunk]
-    int32_t* row_lds = pos_lds + kChunk;                         // [kChunk] (spill mode)
-    float* rel_lds = reinterpret_cast<float*>(row_lds + kChunk);   // [kChunk][NWG <= 4] (token
-                                                                 // scope; the parts' sums)
-    uint8_t* flag_lds = reinterpret_cast<uint8_t*>(rel_lds + 4 * kChunk);   // [kChunk]
-    // the wave-state merge runs after the chunk loop: it reuses the chunk buffers
-    float* merge_lds = reinterpret_cast<float*>(pos_lds);        // [kWaves/2][NV][64]
+    extern __shared__ __align__(16) char lds[];
+    char* tiles = lds;                                            // [kWaves][kWaveLds]
+    float* ml_lds = reinterpret_cast<float*>(lds + kWaves * R::kWaveLds);   // [kWaves][2][G]
+    int32_t* plan_lds = reinterpret_cast<int32_t*>(ml_lds + kWaves * 2 * G);
+    __shared__ int last_arrival;
 
     // the step's first launch advances the device step counter that the
     // end-of-step rebuild reads (a graph replay of the step then sees its step)
     if (a.t_dev && blockIdx.x == 0 && threadIdx.x == 0) *a.t_dev += 1;
-    // The first-tile record of the range this workgroup takes when every
-    // workgroup has one (checked once the ranges are known), requested
-    // together with the counts: with it the first K/V rows are requested
-    // before the chunk's positions and q arrive.
-    constexpr bool kPrefetch = PF && prefetch_shape<BF16, D, G, HKV>();
-    static_assert(!kPrefetch || (TPI == 1 && NWG == 1 && kGroups * TT <= kPlanTokens), "record layout");
-    const int w_full = gridDim.x % 8 == 0 ? (int)((blockIdx.x % 8) * (gridDim.x / 8) + blockIdx.x / 8)
-                                          : (int)blockIdx.x;
-    int rec_b = -1, rec_i0 = 0, rec_len = 0;
-    int rec_pos[kUnroll] = {};
-    if constexpr (kPrefetch) {
-        // a.plan is always set for this variant; the test stays: without it the
-        // compiler scheduled the tile loop differently and the launch took 1.3 %
-        // longer (interleaved runs)
-        if (a.plan) {
-            const int32_t* rec = a.plan + (size_t)w_full * kPlanInts;
-            const int t0 = 4 + wave_uniform(threadIdx.x >> 6) * TT;
-            rec_b = rec[0];
-            rec_i0 = rec[1];
-            rec_len = rec[2];
-#pragma unroll
-            for (int u = 0; u < kUnroll; ++u) rec_pos[u] = rec[t0 + u];
-        }
-    }
-    plan_ranges(a.n_active, a.B, seq_off);
-    __syncthreads();
-    const int T = wave_uniform(seq_off[a.B]);
-    const int Gn = active_groups(T, gridDim.x);
-    if (blockIdx.x == 0) {
-        for (int b = threadIdx.x; b < a.B; b += blockDim.x) {
-            // the workgroups holding the list's first and last real tokens
-            const int x0 = seq_off[b] + kSeqCost, x1 = seq_off[b + 1];
-            a.slot_first[b] = x1 > x0 ? group_of(x0, T, Gn) + b : 0;
-            a.slot_end[b] = x1 > x0 ? group_of(x1 - 1, T, Gn) + b + 1 : 0;
-        }
-    }
-    // the range this workgroup takes.  Workgroups are dealt to the 8 XCDs round
-    // robin; when every workgroup has a range, each XCD takes a contiguous block
-    // of ranges (measured: the slowest XCD's share ends sooner).  Any one-to-one
-    // map gives the same partials, so the results do not depend on it; with
-    // fewer ranges than workgroups the ranges stay spread over the XCDs.
-    const bool blocked = Gn == (int)gridDim.x && gridDim.x % 8 == 0;
-    const int w = blocked ? (int)((blockIdx.x % 8) * (gridDim.x / 8) + blockIdx.x / 8) : (int)blockIdx.x;
-    if (w >= Gn) return;
+    const int hw = a.heads_per_group;             // KV heads a workgroup takes together
+    const int groups = a.Hkv / hw;                // head groups of a sequence
 
     const int wave = wave_uniform(threadIdx.x >> 6);
-    const int wpart = wave % NWG;                 // the wave's share of each token's heads
-    const int wgrp = wave / NWG;                  // the wave's tile group
     const int lane = threadIdx.x & 63;
-    const int slot = lane >> 3;
-    const int tk = slot / SV;                     // token of the iteration
-    const int vh = wpart * SV + slot % SV;        // virtual KV head
-    const int g = vh / kSplit;                    // KV head
-    const int qh0 = g * G + (vh % kSplit) * GS;   // the lane's first query head
-    const int r = lane & 7;
-    const int row_stride = HKV * R::kBytes;       // bytes per token (all KV heads)
-    const int lane_off = g * R::kBytes + r * 16;
+    const int c16 = lane & 15;                    // column (S^T), row of P
+    const int q4 = lane >> 4;
+    const int piece = (lane % R::kLanes) * 16;    // the lane's 16 bytes of a row
+    const int lrow = lane / R::kLanes;            // its row group in a load
+    const int wh = wave % hw;                     // the wave's KV head within the group
+    const int wt = wave / hw;                     // its turn among the tiles
+    const int nwt = kWaves / hw;
+    char* kt = tiles + wave * R::kWaveLds;        // the wave's K tile, then its V tile
+    char* vt = kt;
+    float* rel_kept = reinterpret_cast<float*>(kt + R::kTileLds);  // [tile][wide][kTile]
+    // which 8 bits of p the lane's rows of P carry: leading (0), middle (1), trailing (2 and up)
+    const uint32_t mask1 = c16 / G >= 1 ? 0xFFFF0000u : 0u;
+    const uint32_t mask2 = !kApart && c16 / G >= 2 ? 0xFFFF0000u : 0u;
+    const bool rel_abs = a.rel_mode == 0;
 
-    int x = wave_uniform((int)((int64_t)w * T / Gn));
-    const int x_end = wave_uniform((int)((int64_t)(w + 1) * T / Gn));
-    int b = 0;
-    {
-        int l0 = 0, h0 = a.B - 1;                 // last b with seq_off[b] <= x
-        while (l0 < h0) {
-            const int mid = (l0 + h0 + 1) >> 1;
-            if (wave_uniform(seq_off[mid]) <= x) l0 = mid; else h0 = mid - 1;
-        }
-        b = l0;
-    }
-    bool first_piece = true;
-    while (x < x_end) {
-        while (wave_uniform(seq_off[b + 1]) <= x) ++b;   // skip empty lists
-        const int sb = wave_uniform(seq_off[b]) + kSeqCost;   // the list's first real token
-        const int se = wave_uniform(seq_off[b + 1]);
-        if (x_end <= sb) break;                  // the range ends among the virtual tokens
-        const int nb = se - sb;
-        const int i0 = max(x, sb) - sb;
-        const int i1 = min(se, x_end) - sb;
-        const size_t seq_row = (size_t)b * a.cap;
-        const size_t seg = (size_t)b * a.pool_rows * row_stride;
-        const int32_t* list_b = a.list + seq_row;
-        const int32_t* lrow_b = a.list_row + seq_row;
-        const bool spill = a.spill != 0;
-        const bool rel_abs = a.rel_mode == 0;
-        const bool scope_token = a.scope_token != 0;
-
-        S st;
+    const Plan plan = make_plan(PlanInput{a.n_active, a.B, a.Hkv, hw, a.grid}, kTile, plan_lds);
+    for (int wi = blockIdx.x; wi < plan.live; wi += gridDim.x) {
+    const int w = plan.range_of(wi);
+    int x, x_end;
+    plan.range(w, x, x_end);
+    x = wave_uniform(x);
+    x_end = wave_uniform(x_end);
+    Piece pc;
+    while (next_piece(plan, w, x, x_end, pc)) {
+        constexpr int kPer = 64 / R::kLanes;
+        const int entry = R::kLanes == 8 ? (lane & 7) * 8 + (lane >> 4) * 2 + ((lane >> 3) & 1)
+                                         : (lane % NL) * kPer + lrow;
+        const int b = wave_uniform(pc.b), nb = wave_uniform(pc.n), gi = wave_uniform(pc.group);
+        const int t0 = wave_uniform(pc.t0), t1 = wave_uniform(pc.t1);
+        const int n_parts = wave_uniform(pc.n_parts), part = wave_uniform(pc.part), slot = wave_uniform(pc.slot);
+        const int pair = b * groups + gi;
+        const int g = gi * hw + wh;               // the wave's KV head
+        const size_t pool_row0 = ((size_t)b * a.Hkv + g) * a.pool_rows;
+        const int pool_bytes = a.pool_rows * R::kBytes;
+        const auto rk = buffer((const char*)a.kpool + pool_row0 * R::kBytes, pool_bytes);
+        const auto rv = buffer((const char*)a.vpool + pool_row0 * R::kBytes, pool_bytes);
+        const int32_t* list_b = (a.spill ? a.list_row : a.list) + (size_t)b * a.cap;
+        const auto rl = buffer(list_b, a.cap * 4);
+        const int planes = rel_abs ? groups : a.Hq;
+        const auto rr = buffer(a.rel + (size_t)b * a.planes * a.cap, planes * a.cap * 4);
+        // Load j of a tile takes the tokens j * kPer .. j * kPer + kPer - 1, so that in a
+        // dense list one instruction reads 1 KiB in a row.  Lane i of a row of 16 lanes
+        // holds the list entry that the row's lanes need in load i (a row broadcast
+        // hands it out; where 16 lanes span two tokens, lanes 8 and up hold the second's).
+        // The list's last entry is the new token: its row comes from the arguments, not
+        // from the cache.
+        const int n_cached = nb - 1;
+        auto load_rows = [&](int t) __attribute__((always_inline)) {
+            return __builtin_amdgcn_raw_buffer_load_b32(rl, t < t1 ? (t * kTile + entry) * 4 : kNowhere, 0, 0);
+        };
+        auto row_offsets = [&](int t, int rw, int (&off)[NL]) __attribute__((always_inline)) {
+            const int lim = t < t1 ? n_cached - t * kTile - lrow : 0;
+            unroll<NL>([&](auto J) __attribute__((always_inline)) {
+                constexpr int j = decltype(J)::value;
+                int row = row_bcast<j>(rw);
+                if constexpr (R::kLanes == 8) row = (lane & 8) ? row_bcast<8 + j>(rw) : row;
+                off[j] = j * kPer < lim ? row * R::kBytes + piece : kNowhere;
+            });
+        };
+        // The order of the loop's loads is fixed (the list entries of the tile after
+        // next, the next tile's K rows, its V rows), and the same ahead of the loop, so
+        // that every wait counts exactly what is younger.
+        auto load_tile = [&](__amdgpu_buffer_rsrc_t r, const int (&off)[NL], intx4 (&x)[NL])
+            __attribute__((always_inline)) {
+            __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-        for (int h = 0; h < GS; ++h) {
-            st.m[h] = -INFINITY;
-            st.l[h] = 0.f;
-#pragma unroll
-            for (int e = 0; e < EL; ++e) st.acc[h][e] = 0.f;
-        }
-        const int nbytes = a.pool_rows * row_stride;
-        const __amdgpu_buffer_rsrc_t rk = __builtin_amdgcn_make_buffer_rsrc(
-            (void*)((const char*)a.kpool + seg), (short)0, nbytes, kBufferFlags);
-        const __amdgpu_buffer_rsrc_t rv = __builtin_amdgcn_make_buffer_rsrc(
-            (void*)((const char*)a.vpool + seg), (short)0, nbytes, kBufferFlags);
-
-        for (int c0 = i0; c0 < i1; c0 += kChunk) {
-            const int len = min(kChunk, i1 - c0);
-            // the first tile of the range's first chunk comes from the record when it
-            // describes this chunk and the tile does not reach the appended token
-            uint4 kp[kUnroll][NC], vp[kUnroll][NC];
-            bool have = false;
-            if constexpr (kPrefetch)
-                have = first_piece && c0 == i0 && w == w_full && b == wave_uniform(rec_b) &&
-                       i0 == wave_uniform(rec_i0) && len == wave_uniform(rec_len) && wgrp * TT < len &&
-                       c0 + kGroups * TT < nb && !spill;
-            // a chunk that ends with the new token appends its row to the cache
-            // (a token row is at most 8 heads x 128 x 4 bytes, one 16-byte piece
-            // per thread); its loads overlap the staging loads below
-            const int app_off = threadIdx.x * 16;
-            const bool append = c0 + len == nb && app_off < row_stride;
-            uint4 knew_piece, vnew_piece;
-            int new_row = 0;
-            if (append) {
-                const size_t src = (size_t)b * row_stride + app_off;
-                knew_piece = *reinterpret_cast<const uint4*>((const char*)a.knew + src);
-                vnew_piece = *reinterpret_cast<const uint4*>((const char*)a.vnew + src);
-                // the list's last entry is the new token (its position; its row in spill mode)
-                new_row = spill ? lrow_b[nb - 1] : list_b[nb - 1];
-            }
-            // stage the chunk's positions (and device rows): every load first, then the
-            // stores; the query rows are requested in between, so the chunk's set-up
-            // costs one memory round trip
-            uint4 qr[GS][NC];
-            {
-                int sp[kStage], sr[kStage];
-#pragma unroll
-                for (int k = 0; k < kStage; ++k) {
-                    // every load issued (the last entry past the chunk's end), so the
-                    // waits below count loads instead of waiting for all of them
-                    const int i = min((int)threadIdx.x + k * 64 * kWaves, len - 1);
-                    sp[k] = list_b[c0 + i];
-                    if (spill) sr[k] = lrow_b[c0 + i];
-                }
-                const __amdgpu_buffer_rsrc_t rq = __builtin_amdgcn_make_buffer_rsrc(
-                    (void*)((const char*)a.q + (size_t)b * a.Hq * R::kBytes), (short)0, a.Hq * R::kBytes,
-                    kBufferFlags);
-                const int qo = qh0 * R::kBytes + r * 16;
-#pragma unroll
-                for (int h = 0; h < GS; ++h)
-#pragma unroll
-                    for (int c = 0; c < NC; ++c)
-                        qr[h][c] = __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(
-                            rq, qo + h * R::kBytes + c * 128, 0, 0));
-                // the first tile's rows, requested after the staging loads so that the
-                // staging waits for those only (rows of tokens past the chunk's end: the
-                // tile's first token, as in the tile loop).  Without a record the loads
-                // are still issued, at an offset past the cache's range (a sequence's
-                // rows stay below 2 GiB): they return zeros without a memory access,
-                // and the waits are counted alike on both paths.
-                if constexpr (kPrefetch) {
-#pragma unroll
-                    for (int u = 0; u < kUnroll; ++u) {
-                        const int li = wgrp * TT + u < len ? u : 0;
-                        const int so = have ? wave_uniform(rec_pos[li]) * row_stride : 0;
-#pragma unroll
-                        for (int c = 0; c < NC; ++c) {
-                            const int vo = have ? lane_off + c * 128 : (int)0x80000000;
-                            kp[u][c] = __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(rk, vo, so, kStreamPolicy));
-                            vp[u][c] = __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(rv, vo, so, kStreamPolicy));
-                        }
-                    }
-                }
-#pragma unroll
-                for (int k = 0; k < kStage; ++k) {
-                    const int i = threadIdx.x + k * 64 * kWaves;
-                    if (i < len) {
-                        pos_lds[i] = sp[k];
-                        if (spill) row_lds[i] = sr[k];
-                        flag_lds[i] = 0;
-                    }
-                }
-            }
-            if (append) {
-                const size_t dst = seg + (size_t)new_row * row_stride + app_off;
-                *reinterpret_cast<uint4*>((char*)a.kpool_w + dst) = knew_piece;
-                *reinterpret_cast<uint4*>((char*)a.vpool_w + dst) = vnew_piece;
-            }
-            if (threadIdx.x == 0) tile_lead = 0;
-            __threadfence_block();
-            __syncthreads();
-
-            // One tile: rows kr, vr of the tokens from tb on (rows of tokens past the
-            // chunk's end are the tile's first token's, masked here).
-            auto tile = [&](const uint4 (&kr)[kUnroll][NC], const uint4 (&vr)[kUnroll][NC], int tb)
-                __attribute__((always_inline)) {
-                bool valid[kUnroll];
-#pragma unroll
-                for (int u = 0; u < kUnroll; ++u) valid[u] = tb + u * TPI + tk < len;
-                float xs[kUnroll][GS];
-#pragma unroll
-                for (int u = 0; u < kUnroll; ++u)
-#pragma unroll
-                    for (int h = 0; h < GS; ++h) xs[u][h] = lane_dot<BF16, D>(kr[u], qr[h]);
-                // 8-lane sums (every lane of a slot ends with the same bits)
-#pragma unroll
-                for (int u = 0; u < kUnroll; ++u)
-#pragma unroll
-                    for (int h = 0; h < GS; ++h) xs[u][h] += dpp_mov<0xB1>(xs[u][h]);   // quad_perm [1,0,3,2]
-#pragma unroll
-                for (int u = 0; u < kUnroll; ++u)
-#pragma unroll
-                    for (int h = 0; h < GS; ++h) xs[u][h] += dpp_mov<0x4E>(xs[u][h]);   // quad_perm [2,3,0,1]
-#pragma unroll
-                for (int u = 0; u < kUnroll; ++u)
-#pragma unroll
-                    for (int h = 0; h < GS; ++h) xs[u][h] += dpp_mov<0x141>(xs[u][h]);  // row_half_mirror
-
-                // relevance (Eq. 2): sum over the slot's heads, then over the token's KV-head slots
+            for (int j = 0; j < NL; ++j) x[j] = load16<kStreamPolicy>(r, off[j]);
+            __builtin_amdgcn_sched_barrier(0);
+        };
+        // The relevance values stay in LDS and are stored together, at the piece's end or
+        // when the room is full, summed over the workgroup's KV heads: stored tile by
+        // tile among the row loads they cost as much as ten times their bytes (a launch
+        // over 8 x 32k tokens took 178 instead of 166 us with 8 MB of them).
+        const int wide = rel_abs ? 1 : G;         // planes of a KV head
+        const bool keeps = c16 < wide;            // lanes that hold a value to keep
+        const int chunk = R::kRelLds / (kTile * 4) / wide * nwt;   // tiles the room is for
+        const auto store_kept = [&](int c0, int c1) __attribute__((always_inline)) {
+            const int per_wave = (c1 - c0 + nwt - 1) / nwt;
+            const int n4 = rel_abs ? (c1 - c0) * (kTile / 4) : kWaves * per_wave * wide * (kTile / 4);
+            for (int e = threadIdx.x; e < n4; e += kThreads) {
+                const int o = e % (kTile / 4), row = e / (kTile / 4);
+                floatx4 v = {0.f, 0.f, 0.f, 0.f};
+                int at;
                 if (rel_abs) {
+                    const int turn = row % nwt, idx = row / nwt;
+                    for (int h = 0; h < hw; ++h)
+                        v += *reinterpret_cast<const floatx4*>(
+                            tiles + (h + hw * turn) * R::kWaveLds + R::kTileLds + (idx * kTile + o * 4) * 4);
+                    at = gi * a.cap + (c0 + row) * kTile + o * 4;
+                } else {
+                    const int c = row % wide, idx = row / wide % per_wave, wv = row / wide / per_wave;
+                    const int tile = c0 + wv / hw + idx * nwt;
+                    v = *reinterpret_cast<const floatx4*>(tiles + wv * R::kWaveLds + R::kTileLds +
+                                                          ((idx * wide + c) * kTile + o * 4) * 4);
+                    at = ((gi * hw + wv % hw) * G + c) * a.cap + tile * kTile + o * 4;
+                    if (tile >= c1) at = kNowhere / 4;
+                }
+                __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(uintx4, v), rr, at * 4, 0, kStreamPolicy);
+            }
+        };
+
+        int t = t0 + wt;
+        int rows = load_rows(t);
+        // the query heads of the wave's KV head, as columns (repeated)
+        intx4 qf[NQ];
+        {
+            const auto rq = buffer((const char*)a.q + (size_t)b * a.Hq * R::kBytes, a.Hq * R::kBytes);
+            const int qo = (g * G + c16 % G) * R::kBytes + q4 * 16;
 #pragma unroll
-                    for (int u = 0; u < kUnroll; ++u) {
-                        float rel = 0.f;
+            for (int s = 0; s < NQ; ++s) qf[s] = load16<0>(rq, qo + s * 64);
+        }
+        // the new token's rows, for the wave whose tile holds it
+        const int t_new = n_cached / kTile;
+        const bool owns_new = t_new >= t0 && t_new < t1 && (t_new - t0) % nwt == wt;
+        intx4 k_new, v_new;
+        int new_row;
+        {
+            const int span = a.B * a.Hkv * R::kBytes;
+            const int no = owns_new && lane < R::kLanes ? (b * a.Hkv + g) * R::kBytes + piece : kNowhere;
+            k_new = load16<0>(buffer(a.knew, span), no);
+            v_new = load16<0>(buffer(a.vnew, span), no);
+            new_row = __builtin_amdgcn_raw_buffer_load_b32(rl, owns_new ? n_cached * 4 : kNowhere, 0, 0);
+        }
+        intx4 kx[NL], vx[NL];
+        int off[NL];
+        int next_rows = load_rows(t + nwt);
+        row_offsets(t, rows, off);
+        load_tile(rk, off, kx);
+        load_tile(rv, off, vx);
+
+        float m = -INFINITY, l = 0.f;             // of the lane's column (l: its own tokens)
+        floatx4 acc[NB], acc2[kApart ? NB : 1];
 #pragma unroll
-                        for (int h = 0; h < GS; ++h) rel += fabsf(xs[u][h]);
-                        if constexpr (SV >= 2) rel += lane_xor<8>(rel);
-                        if constexpr (SV >= 4) rel += lane_xor<16>(rel);
-                        if constexpr (SV >= 8) rel += lane_xor<32>(rel);
-                        if (valid[u] && slot % SV == 0 && r == 0) {
-                            if (NWG > 1) {
-                                // this wave's part of the sum: the parts meet after the tiles
-                                rel_lds[(tb + u * TPI + tk) * NWG + wpart] = rel;
-                            } else if (scope_token) {
-                                rel_lds[tb + u * TPI + tk] = rel;
-                            } else {                      // the freeze loop picks the candidates
-                                const int f = (rel < a.tau_H ? 1 : 0) |
-                                              (fabsf(rel - a.tau_H) < a.margin_H ? 2 : 0);
-                                if (f) flag_lds[tb + u * TPI + tk] = (uint8_t)f;
+        for (int k = 0; k < NB; ++k) {
+            acc[k] = floatx4{0.f, 0.f, 0.f, 0.f};
+            if constexpr (kApart) acc2[k] = floatx4{0.f, 0.f, 0.f, 0.f};
+        }
+
+        int c0 = t0;                              // first tile of the chunk
+        for (;;) {
+        const int c1 = min(t1, c0 + chunk);
+        int kept = 0;
+        for (; t < c1; t += nwt) {
+            // K: registers -> LDS, then request the next tile's
+#pragma unroll
+            for (int j = 0; j < NL; ++j)
+                *reinterpret_cast<intx4*>(kt + (j * kPer + lrow) * R::kKStride + piece) = kx[j];
+            if (t == t_new && lane < R::kLanes)
+                *reinterpret_cast<intx4*>(kt + (n_cached % kTile) * R::kKStride + piece) = k_new;
+            __builtin_amdgcn_wave_barrier();
+            rows = next_rows;
+            next_rows = load_rows(t + 2 * nwt);
+            row_offsets(t + nwt, rows, off);
+            load_tile(rk, off, kx);
+
+            // scores: rows = tokens 4 q4 + i (+ 16), column = the lane's head
+            // several shorter chains, added at the end: less rounding, less latency
+            constexpr int kChains = BF16 ? 2 : 4;
+            floatx4 s[NBLK], sp[NBLK][kChains] = {};
+#pragma unroll
+            for (int k = 0; k < NQ; ++k) {
+#pragma unroll
+                for (int blk = 0; blk < NBLK; ++blk) {
+                    const intx4 kr = *reinterpret_cast<const intx4*>(kt + (blk * 16 + c16) * R::kKStride +
+                                                                     k * 64 + q4 * 16);
+                    if constexpr (BF16) {
+                        sp[blk][k % 2] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+                            __builtin_bit_cast(bf16x8, kr), __builtin_bit_cast(bf16x8, qf[k]), sp[blk][k % 2], 0, 0, 0);
+                    } else {
+#pragma unroll
+                        for (int e = 0; e < 4; ++e)
+                            sp[blk][e] = __builtin_amdgcn_mfma_f32_16x16x4f32(
+                                __int_as_float(kr[e]), __int_as_float(qf[k][e]), sp[blk][e], 0, 0, 0);
+                    }
+                }
+            }
+#pragma unroll
+            for (int blk = 0; blk < NBLK; ++blk) {
+                s[blk] = sp[blk][0] + sp[blk][1];
+                if constexpr (!BF16) s[blk] += sp[blk][2] + sp[blk][3];
+            }
+            // V: the same, in the same place
+            __builtin_amdgcn_wave_barrier();
+#pragma unroll
+            for (int j = 0; j < NL; ++j)
+                *reinterpret_cast<intx4*>(vt + (j * kPer + lrow) * R::kVStride + piece) = vx[j];
+            if (t == t_new && lane < R::kLanes)
+                *reinterpret_cast<intx4*>(vt + (n_cached % kTile) * R::kVStride + piece) = v_new;
+            __builtin_amdgcn_wave_barrier();
+            load_tile(rv, off, vx);
+
+            float y[NBLK][4];
+            const int left = nb - t * kTile - q4 * 4;     // tokens from the lane's first one on
+#pragma unroll
+            for (int blk = 0; blk < NBLK; ++blk)
+#pragma unroll
+                for (int i = 0; i < 4; ++i)
+                    y[blk][i] = blk * 16 + i < left ? s[blk][i] * a.scale_log2 : -INFINITY;
+            // relevance: the sum of |q.k| over the KV head's query heads (neighbouring
+            // columns), or the logits themselves.  Entries past the list's end are
+            // kept too (the planes have room, nothing reads them).
+#pragma unroll
+            for (int blk = 0; blk < NBLK; ++blk) {
+                floatx4 v;
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    float r = fabsf(s[blk][i]);
+                    if constexpr (G >= 2) r += dpp_mov<0xB1>(r);     // quad_perm [1,0,3,2]
+                    if constexpr (G >= 4) r += dpp_mov<0x4E>(r);     // quad_perm [2,3,0,1]
+                    if constexpr (G >= 8) r += dpp_mov<0x141>(r);    // row_half_mirror
+                    v[i] = rel_abs ? r : y[blk][i];
+                }
+                if (keeps)
+                    *reinterpret_cast<floatx4*>(rel_kept + (kept * wide + c16) * kTile + blk * 16 + q4 * 4) = v;
+            }
+            ++kept;
+            // online softmax
+            float top = y[0][0];
+#pragma unroll
+            for (int blk = 0; blk < NBLK; ++blk)
+#pragma unroll
+                for (int i = 0; i < 4; ++i) top = fmaxf(top, y[blk][i]);
+            if (__any(top > m + kMaxLag)) {
+                top = fmaxf(top, __shfl_xor(top, 16));
+                top = fmaxf(top, __shfl_xor(top, 32));
+                const float mn = fmaxf(m, top);
+                const float sc = m < mn ? __builtin_amdgcn_exp2f(m - mn) : 1.f;
+                l *= sc;
+                m = mn;
+                float row_sc[4];
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {     // the scale of row 4 q4 + i: head (4 q4 + i) % G
+                    row_sc[i] = __shfl(sc, (q4 * 4 + i) % G);
+                }
+#pragma unroll
+                for (int k = 0; k < NB; ++k)
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) {
+                        acc[k][i] *= row_sc[i];
+                        if constexpr (kApart) acc2[k][i] *= row_sc[i];
+                    }
+            }
+            float p[NBLK][4];
+#pragma unroll
+            for (int blk = 0; blk < NBLK; ++blk)
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    p[blk][i] = __builtin_amdgcn_exp2f(y[blk][i] - m);
+                    l += p[blk][i];
+                }
+            if constexpr (BF16) {
+                // the lane's part of every weight, as the rows of P
+                int pw[2 * NBLK], pw2[2 * NBLK];
+#pragma unroll
+                for (int blk = 0; blk < NBLK; ++blk)
+#pragma unroll
+                    for (int i = 0; i < 4; i += 2) {
+                        uint32_t u[2], u2[2];
+#pragma unroll
+                        for (int e = 0; e < 2; ++e) {
+                            float f = p[blk][i + e];
+                            f -= __uint_as_float(__float_as_uint(f) & mask1);
+                            f -= __uint_as_float(__float_as_uint(f) & mask2);
+                            u[e] = __float_as_uint(f);
+                            if constexpr (kApart) {
+                                float lo = p[blk][i + e];
+                                lo -= __uint_as_float(__float_as_uint(lo) & 0xFFFF0000u);
+                                lo -= __uint_as_float(__float_as_uint(lo) & 0xFFFF0000u);
+                                u2[e] = __float_as_uint(lo);
+                            }
+                        }
+                        pw[blk * 2 + i / 2] = (int)__builtin_amdgcn_perm(u[1], u[0], 0x07060302u);
+                        if constexpr (kApart) pw2[blk * 2 + i / 2] = (int)__builtin_amdgcn_perm(u2[1], u2[0], 0x07060302u);
+                    }
+                // V's columns: 4 tokens per transposed read (rows 4 q4 .. 4 q4 + 3 of a block)
+                const char* vb = vt + (q4 * 4 + c16 / 4) * R::kVStride + (c16 % 4) * 8;
+#pragma unroll
+                for (int k = 0; k < NB; ++k) {
+                    auto column = [&](int blk) __attribute__((always_inline)) {
+                        return __builtin_amdgcn_ds_read_tr16_b64_v4i16(
+                            (lds_shortx4)(vb + blk * 16 * R::kVStride + k * 32));
+                    };
+                    if constexpr (NBLK == 1) {
+                        const shortx4 v = column(0);
+                        acc[k] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(
+                            __builtin_bit_cast(shortx4, intx2{pw[0], pw[1]}), v, acc[k], 0, 0, 0);
+                        if constexpr (kApart)
+                            acc2[k] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(
+                                __builtin_bit_cast(shortx4, intx2{pw2[0], pw2[1]}), v, acc2[k], 0, 0, 0);
+                    } else {
+#pragma unroll
+                        for (int j = 0; j < NBLK; j += 2) {
+                            const bf16x8 v = __builtin_bit_cast(
+                                bf16x8, __builtin_shufflevector(column(j), column(j + 1), 0, 1, 2, 3, 4, 5, 6, 7));
+                            const int* w = pw + 2 * j;
+                            acc[k] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+                                __builtin_bit_cast(bf16x8, intx4{w[0], w[1], w[2], w[3]}), v, acc[k], 0, 0, 0);
+                            if constexpr (kApart) {
+                                const int* w2 = pw2 + 2 * j;
+                                acc2[k] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+                                    __builtin_bit_cast(bf16x8, intx4{w2[0], w2[1], w2[2], w2[3]}), v, acc2[k], 0, 0, 0);
                             }
                         }
                     }
                 }
+            } else {
+                // the tile's sums apart, then added: a chain of one addition per tile
+                // instead of per token keeps the rounding error down
+#pragma unroll
+                for (int k = 0; k < NB; ++k) {
+                    floatx4 part = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                    for (int blk = 0; blk < NBLK; ++blk)
+#pragma unroll
+                        for (int i = 0; i < 4; ++i) {
+                            const float v = *reinterpret_cast<const float*>(
+                                vt + (blk * 16 + q4 * 4 + i) * R::kVStride + (k * 16 + c16) * 4);
+                            part = __builtin_amdgcn_mfma_f32_16x16x4f32(p[blk][i], v, part, 0, 0, 0);
+                        }
+                    acc[k] += part;
+                }
+            }
+        }
+        if (c1 == t1) break;
+        lds_barrier();
+        store_kept(c0, c1);
+        lds_barrier();
+        c0 = c1;
+        }
+        if (owns_new && lane < R::kLanes) {       // the append
+            const size_t dst = (pool_row0 + new_row) * R::kBytes + piece;
+            *reinterpret_cast<intx4*>((char*)a.kpool_w + dst) = k_new;
+            *reinterpret_cast<intx4*>((char*)a.vpool_w + dst) = v_new;
+        }
 
-                float y[kUnroll][GS];
+        // ---- merge the waves: every wave's state (its head's G x D sums) into its own tile ----
+        l += __shfl_xor(l, 16);
+        l += __shfl_xor(l, 32);
+        if (lane < G) {
+            ml_lds[(wave * 2) * G + lane] = m;
+            ml_lds[(wave * 2 + 1) * G + lane] = l;
+        }
+        store_state<BF16, D, G>(acc, acc2, reinterpret_cast<float*>(kt), lane);
+        lds_barrier();
+        const int heads = hw * G;                 // query heads of the piece
+        const size_t slot0 = (size_t)(slot - part) * heads;        // the pair's first partial
+        const Finish fin{a.out + ((size_t)b * a.Hq + gi * heads) * D,
+                         a.norm ? a.norm + ((size_t)b * a.Hq + gi * heads) * 2 : nullptr};
+        // partials: offsets stay far below 2 GiB (32 MiB at the widest layout and batch 1024)
+        const auto rp = buffer(a.part_acc, 0x7FFFFFFF), rm = buffer(a.part_ml, 0x7FFFFFFF);
+        // four dims of a head per thread
+        for (int e = threadIdx.x * 4; e < heads * D; e += kThreads * 4) {
+            const int hh = e / D, d = e % D;
+            const int h = hh % G, h_kv = hh / G;
+            float mw[kWaves], lw[kWaves];
+            floatx4 ow[kWaves];
 #pragma unroll
-                for (int u = 0; u < kUnroll; ++u)
+            for (int j = 0; j < kWaves; ++j) {    // every wave has a state, empty ones with m = -inf
+                const int wv = min(h_kv + hw * j, kWaves - 1);
+                mw[j] = j < nwt ? ml_lds[(wv * 2) * G + h] : -INFINITY;
+                lw[j] = ml_lds[(wv * 2 + 1) * G + h];
+                ow[j] = *reinterpret_cast<const floatx4*>(tiles + wv * R::kWaveLds + (h * (D + 4) + d) * 4);
+            }
+            float M = mw[0];
 #pragma unroll
-                    for (int h = 0; h < GS; ++h) y[u][h] = valid[u] ? xs[u][h] * a.scale_log2 : -INFINITY;
-                if (!rel_abs) {
-                    // relevance by attention weight needs the sequence's normaliser: keep the logits
+            for (int j = 1; j < kWaves; ++j) M = fmaxf(M, mw[j]);
+            float L = 0.f;
+            floatx4 o = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-                    for (int u = 0; u < kUnroll; ++u) {
-                        if (valid[u] && r == 0) {
-                            float* xl = a.xlog + (seq_row + c0 + tb + u * TPI + tk) * a.Hq + qh0;
+            for (int j = 0; j < kWaves; ++j) {
+                if (mw[j] != -INFINITY) fold(L, o, __builtin_amdgcn_exp2f(mw[j] - M), lw[j], ow[j]);
+            }
+            if (n_parts == 1) {
+                fin.template write<D>(hh, d, M, L, o);
+            } else {
+                const size_t slot_h = slot0 + (size_t)part * heads + hh;
+                __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(uintx4, o), rp, (int)(slot_h * D + d) * 4, 0,
+                                                       kAgentScope);
+                if (d == 0)
+                    __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(uintx2, floatx2{M, L}), rm,
+                                                          (int)slot_h * 8, 0, kAgentScope);
+            }
+        }
+        if (n_parts > 1) {
+            // the device-scope stores of every thread have completed before the
+            // ticket is taken, so no cache-wide write-back is needed
+            __builtin_amdgcn_s_waitcnt(0);
+            lds_barrier();
+            if (threadIdx.x == 0)
+                last_arrival = __hip_atomic_fetch_add(a.ticket + pair, 1, __ATOMIC_RELAXED,
+                                                      __HIP_MEMORY_SCOPE_AGENT) == n_parts - 1;
+            lds_barrier();
+            if (last_arrival) {
+                // The pair's partials, read at device scope (they may sit in another
+                // XCD's L2).  kSlotGroups groups of threads each fold every
+                // kSlotGroups-th slot, all loads of a pass in flight, and the groups'
+                // states are folded in order: one or two round trips for the 16 to
+                // 32 parts of a lone sequence.
+                constexpr int kFoldThreads = G * D / 4 < kThreads ? G * D / 4 : kThreads;
+                constexpr int kSlotGroups = kThreads / kFoldThreads < 16 ? kThreads / kFoldThreads : 16;
+                constexpr int kPass = 4;
+                const int grp = threadIdx.x / kFoldThreads;
+                // a thread's state, in its wave's tile (the relevance values are still kept)
+                auto fold_o = [&](int th) { return reinterpret_cast<floatx4*>(tiles + th / 64 * R::kWaveLds) + th % 64; };
+                auto fold_ml = [&](int th) { return reinterpret_cast<float*>(tiles + th / 64 * R::kWaveLds + 1024) + th % 64 * 2; };
+                for (int e0 = 0; e0 < heads * D; e0 += kFoldThreads * 4) {
+                    const int e = e0 + threadIdx.x % kFoldThreads * 4;
+                    const int hh = e / D, d = e % D;
+                    float M = -INFINITY, L = 0.f;
+                    floatx4 o = {0.f, 0.f, 0.f, 0.f};
+                    for (int k = grp; k < n_parts && grp < kSlotGroups; k += kSlotGroups * kPass) {
+                        floatx2 pml[kPass];
+                        floatx4 po[kPass];
 #pragma unroll
-                            for (int h = 0; h < GS; ++h) xl[h] = y[u][h];
+                        for (int u = 0; u < kPass; ++u) {
+                            const size_t slot_h = slot0 + (size_t)min(k + u * kSlotGroups, n_parts - 1) * heads + hh;
+                            pml[u] = __builtin_bit_cast(floatx2, __builtin_amdgcn_raw_buffer_load_b64(
+                                rm, (int)slot_h * 8, 0, kAgentScope));
+                            po[u] = __builtin_bit_cast(floatx4, load16<kAgentScope>(rp, (int)(slot_h * D + d) * 4));
+                        }
+                        float Mn = M;
+#pragma unroll
+                        for (int u = 0; u < kPass; ++u)
+                            if (k + u * kSlotGroups < n_parts) Mn = fmaxf(Mn, pml[u][0]);
+                        const float sc = M == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(M - Mn);
+                        L *= sc;
+                        o *= sc;
+#pragma unroll
+                        for (int u = 0; u < kPass; ++u)
+                            if (k + u * kSlotGroups < n_parts)
+                                fold(L, o, __builtin_amdgcn_exp2f(pml[u][0] - Mn), pml[u][1], po[u]);
+                        M = Mn;
+                    }
+                    if constexpr (kSlotGroups > 1) {
+                        lds_barrier();
+                        fold_ml(threadIdx.x)[0] = M;
+                        fold_ml(threadIdx.x)[1] = L;
+                        *fold_o(threadIdx.x) = o;
+                        lds_barrier();
+                        if (grp == 0) {
+                            float Mt = M;
+#pragma unroll
+                            for (int k = 1; k < kSlotGroups; ++k)
+                                Mt = fmaxf(Mt, fold_ml(threadIdx.x + k * kFoldThreads)[0]);
+                            const float s0 = __builtin_amdgcn_exp2f(M - Mt);
+                            L *= s0;
+                            o *= s0;
+#pragma unroll
+                            for (int k = 1; k < kSlotGroups; ++k) {
+                                const int src = threadIdx.x + k * kFoldThreads;
+                                const float mk = fold_ml(src)[0];
+                                if (mk != -INFINITY)
+                                    fold(L, o, __builtin_amdgcn_exp2f(mk - Mt), fold_ml(src)[1], *fold_o(src));
+                            }
+                            M = Mt;
                         }
                     }
+                    if (grp == 0) fin.template write<D>(hh, d, M, L, o);
                 }
-#pragma unroll
-                for (int h = 0; h < GS; ++h) {
-                    float mt = st.m[h];
-#pragma unroll
-                    for (int u = 0; u < kUnroll; ++u) mt = fmaxf(mt, y[u][h]);
-                    if (__any(mt > st.m[h])) {
-                        const float sc = (mt > st.m[h]) ? __builtin_amdgcn_exp2f(st.m[h] - mt) : 1.f;
-                        st.l[h] *= sc;
-#pragma unroll
-                        for (int e = 0; e < EL; ++e) st.acc[h][e] *= sc;
-                        st.m[h] = mt;
-                    }
-                }
-#pragma unroll
-                for (int u = 0; u < kUnroll; ++u) {
-#pragma unroll
-                    for (int h = 0; h < GS; ++h) {
-                        const float pr = valid[u] ? __builtin_amdgcn_exp2f(y[u][h] - st.m[h]) : 0.f;
-                        st.l[h] += pr;
-                        lane_axpy<BF16, D>(st.acc[h], pr, vr[u]);
-                    }
-                }
-                // Pacing.  The tiles are dealt statically (every run sums in the same
-                // order), but when several waves can issue the hardware favours the
-                // older ones, and over a long range the younger waves fall behind by
-                // about a tenth.  A wave that has finished fewer tiles than the
-                // workgroup's leader issues at a raised priority until it catches up.
-                {
-                    const unsigned done = (unsigned)((tb - wgrp * TT) / (kGroups * TT) + 1);
-                    unsigned lead = 0;
-                    if (lane == 0) lead = atomicMax(&tile_lead, done);
-                    if (done < (unsigned)wave_uniform((int)lead)) __builtin_amdgcn_s_setprio(2);
-                    else __builtin_amdgcn_s_setprio(0);
-                }
-            };
-            int tb0 = wgrp * TT;
-            if constexpr (kPrefetch) {
-                if (have) {                       // rows requested with the staging loads
-                    tile(kp, vp, tb0);
-                    tb0 += kGroups * TT;
-                }
-            }
-            for (int tb = tb0; tb < len; tb += kGroups * TT) {
-                uint4 kr[kUnroll][NC], vr[kUnroll][NC];
-#pragma unroll
-                for (int u = 0; u < kUnroll; ++u) {
-                    const int idx = tb + u * TPI + tk;
-                    const int li = idx < len ? idx : tb;
-                    const int drow = spill ? row_lds[li] : pos_lds[li];     // device row of the token
-                    int vo = lane_off, so = 0;
-                    if constexpr (TPI == 1) so = wave_uniform(drow) * row_stride;
-                    else vo += drow * row_stride;
-#pragma unroll
-                    for (int c = 0; c < NC; ++c) {
-                        kr[u][c] = __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(rk, vo + c * 128, so, kStreamPolicy));
-                        vr[u][c] = __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(rv, vo + c * 128, so, kStreamPolicy));
-                    }
-                }
-                tile(kr, vr, tb);
-            }
-            __builtin_amdgcn_s_setprio(0);
-            __syncthreads();
-
-            if constexpr (NWG > 1) {
-                // the token's score is the sum of its parts (fixed order); in layer
-                // scope it decides the flag here, in token scope the sum is kept below
-#pragma unroll
-                for (int k = 0; k < kStage; ++k) {
-                    const int i = threadIdx.x + k * 64 * kWaves;
-                    if (i < len) {
-                        float sum = 0.f;
-#pragma unroll
-                        for (int p2 = 0; p2 < NWG; ++p2) sum += rel_lds[i * NWG + p2];
-                        if (scope_token) rel_lds[i * NWG] = sum;
-                        else flag_lds[i] = rel_abs ? (uint8_t)((sum < a.tau_H ? 1 : 0) |
-                                                               (fabsf(sum - a.tau_H) < a.margin_H ? 2 : 0))
-                                                   : (uint8_t)0;
-                    }
-                }
-            }
-            if (scope_token && rel_abs) {
-                // token scope sums the score over the layers; the freeze loop runs at the step's end
-                float prev[kStage];
-#pragma unroll
-                for (int k = 0; k < kStage; ++k) {
-                    const int i = threadIdx.x + k * 64 * kWaves;
-                    prev[k] = (i < len && !a.first_layer) ? a.rel_acc[seq_row + pos_lds[i]] : 0.f;
-                }
-#pragma unroll
-                for (int k = 0; k < kStage; ++k) {
-                    const int i = threadIdx.x + k * 64 * kWaves;
-                    if (i < len) a.rel_acc[seq_row + pos_lds[i]] = prev[k] + rel_lds[i * NWG];
-                }
-            }
-            // score flags of the chunk's tokens (s_j < tau), one byte per position, for
-            // the freeze loop of the end-of-step rebuild (which tests the window)
-            if (rel_abs && !scope_token) {
-#pragma unroll
-                for (int k = 0; k < kStage; ++k) {
-                    const int i = threadIdx.x + k * 64 * kWaves;
-                    if (i < len) a.flag[seq_row + pos_lds[i]] = flag_lds[i];
-                }
-            }
-            __syncthreads();                       // LDS chunk buffers are reused next
-        }
-
-        if constexpr (kOneRound) {
-            // merge the wave states in one round: every wave stores its state, then
-            // each wave folds the states of its part's waves for its own rows
-            // (fixed order)
-            __syncthreads();
-            {
-                float* dst = merge_lds + (size_t)wave * NV * 64 + lane;
-#pragma unroll
-                for (int h = 0; h < GS; ++h) {
-                    dst[(2 * h) * 64] = st.m[h];
-                    dst[(2 * h + 1) * 64] = st.l[h];
-#pragma unroll
-                    for (int e = 0; e < EL; ++e) dst[(2 * GS + h * EL + e) * 64] = st.acc[h][e];
-                }
-            }
-            __syncthreads();
-            // the states of the waves of one part cover the same heads: fold those
-            constexpr int kPerPart = kWaves / NWG;
-            constexpr int RPW = GS * EL / kPerPart;       // acc rows folded by each wave
-            const int row0 = wgrp * RPW;                  // first row, within head hh
-            const int hh = row0 / EL, e0 = row0 % EL;
-            float M = -INFINITY;
-            float ms[kPerPart];
-#pragma unroll
-            for (int j = 0; j < kPerPart; ++j) {
-                const int s2 = j * NWG + wpart;           // the part's waves, in order
-                ms[j] = merge_lds[((size_t)s2 * NV + 2 * hh) * 64 + lane];
-                M = fmaxf(M, ms[j]);
-            }
-            float Lf = 0.f, accf[RPW];
-#pragma unroll
-            for (int i = 0; i < RPW; ++i) accf[i] = 0.f;
-#pragma unroll
-            for (int j = 0; j < kPerPart; ++j) {
-                const int s2 = j * NWG + wpart;
-                const float wgt = (ms[j] == -INFINITY) ? 0.f : __builtin_amdgcn_exp2f(ms[j] - M);
-                Lf = fmaf(wgt, merge_lds[((size_t)s2 * NV + 2 * hh + 1) * 64 + lane], Lf);
-#pragma unroll
-                for (int i = 0; i < RPW; ++i)
-                    accf[i] = fmaf(wgt, merge_lds[((size_t)s2 * NV + 2 * GS + hh * EL + e0 + i) * 64 + lane], accf[i]);
-            }
-            // slots holding the same KV head (different tokens of an iteration)
-#pragma unroll
-            for (int mask = 8 * SV; mask < 64; mask <<= 1) {
-                const float om = __shfl_xor(M, mask), ol = __shfl_xor(Lf, mask);
-                float oa[RPW];
-#pragma unroll
-                for (int i = 0; i < RPW; ++i) oa[i] = __shfl_xor(accf[i], mask);
-                // fixed order: the lower lane's state first
-                const bool up = (lane & mask) != 0;
-                const float m1 = up ? om : M, m2 = up ? M : om;
-                const float Mn = fmaxf(m1, m2);
-                const float w1 = (m1 == -INFINITY) ? 0.f : __builtin_amdgcn_exp2f(m1 - Mn);
-                const float w2 = (m2 == -INFINITY) ? 0.f : __builtin_amdgcn_exp2f(m2 - Mn);
-                const float l1 = up ? ol : Lf, l2 = up ? Lf : ol;
-                Lf = l1 * w1 + l2 * w2;
-#pragma unroll
-                for (int i = 0; i < RPW; ++i) {
-                    const float a1 = up ? oa[i] : accf[i], a2 = up ? accf[i] : oa[i];
-                    accf[i] = a1 * w1 + a2 * w2;
-                }
-                M = Mn;
-            }
-            __syncthreads();                       // merge buffer reads done: chunks may restage
-            if (tk == 0) {
-                const size_t part = (size_t)(w + b) * a.Hq + (size_t)qh0 + hh;
-                float* dst = a.part_acc + part * D;
-#pragma unroll
-                for (int i = 0; i < RPW; ++i) {
-                    const int e = e0 + i;
-                    dst[(e / R::kPerChunk) * (128 / R::kElem) + r * R::kPerChunk + (e % R::kPerChunk)] = accf[i];
-                }
-                if (r == 0 && e0 == 0) {
-                    a.part_ml[part * 2 + 0] = M;
-                    a.part_ml[part * 2 + 1] = Lf;
-                }
-            }
-        } else {
-        // merge the waves' states: a fixed tree through LDS (4 -> 2 -> 1 partners)
-#pragma unroll
-        for (int half = kWaves / 2; half >= NWG; half >>= 1) {
-            __syncthreads();
-            if (wave >= half && wave < 2 * half) {
-                float* dst = merge_lds + (size_t)(wave - half) * NV * 64 + lane;
-#pragma unroll
-                for (int h = 0; h < GS; ++h) {
-                    dst[(2 * h) * 64] = st.m[h];
-                    dst[(2 * h + 1) * 64] = st.l[h];
-#pragma unroll
-                    for (int e = 0; e < EL; ++e) dst[(2 * GS + h * EL + e) * 64] = st.acc[h][e];
-                }
-            }
-            __syncthreads();
-            if (wave < half) {
-                const float* src = merge_lds + (size_t)wave * NV * 64 + lane;
-                float bm[GS], bl[GS], bacc[GS][EL];
-#pragma unroll
-                for (int h = 0; h < GS; ++h) {
-                    bm[h] = src[(2 * h) * 64];
-                    bl[h] = src[(2 * h + 1) * 64];
-#pragma unroll
-                    for (int e = 0; e < EL; ++e) bacc[h][e] = src[(2 * GS + h * EL + e) * 64];
-                }
-                fold<BF16, D, GS>(st, bm, bl, bacc);
+                if (threadIdx.x == 0) a.ticket[pair] = 0;      // ready for the next launch
             }
         }
-        __syncthreads();                           // merge buffer reads done: chunks may restage
-        if (wave < NWG) {
-            // merge the slots that hold the same KV head (different tokens of an iteration)
-#pragma unroll
-            for (int mask = 8 * SV; mask < 64; mask <<= 1) {
-                float bm[GS], bl[GS], bacc[GS][EL];
-#pragma unroll
-                for (int h = 0; h < GS; ++h) {
-                    bm[h] = __shfl_xor(st.m[h], mask);
-                    bl[h] = __shfl_xor(st.l[h], mask);
-#pragma unroll
-                    for (int e = 0; e < EL; ++e) bacc[h][e] = __shfl_xor(st.acc[h][e], mask);
-                }
-                // fold in a fixed order: the lower lane's state first
-                if (lane & mask) {
-#pragma unroll
-                    for (int h = 0; h < GS; ++h) {
-                        const float tm = st.m[h], tl = st.l[h];
-                        st.m[h] = bm[h]; bm[h] = tm;
-                        st.l[h] = bl[h]; bl[h] = tl;
-#pragma unroll
-                        for (int e = 0; e < EL; ++e) {
-                            const float ta = st.acc[h][e];
-                            st.acc[h][e] = bacc[h][e];
-                            bacc[h][e] = ta;
-                        }
-                    }
-                }
-                fold<BF16, D, GS>(st, bm, bl, bacc);
-            }
-            // partial of (workgroup w, sequence b): slot (token 0, virtual head vh) writes
-            // query heads qh0 .. qh0 + GS - 1
-            if (tk == 0) {
-                const size_t part = (size_t)(w + b) * a.Hq + (size_t)qh0;
-#pragma unroll
-                for (int h = 0; h < GS; ++h) {
-                    float* dst = a.part_acc + (part + h) * D;
-#pragma unroll
-                    for (int c = 0; c < NC; ++c)
-#pragma unroll
-                        for (int i = 0; i < R::kPerChunk; i += 4) {
-                            const int e = c * R::kPerChunk + i;
-                            *reinterpret_cast<float4*>(dst + c * (128 / R::kElem) + r * R::kPerChunk + i) =
-                                make_float4(st.acc[h][e], st.acc[h][e + 1], st.acc[h][e + 2], st.acc[h][e + 3]);
-                        }
-                    if (r == 0) {
-                        a.part_ml[(part + h) * 2 + 0] = st.m[h];
-                        a.part_ml[(part + h) * 2 + 1] = st.l[h];
-                    }
-                }
-            }
-        }
-        }
-        first_piece = false;
-        x = sb + i1;
+        store_kept(c0, t1);
+        lds_barrier();                           // the wave states have been read: tiles may be rewritten
     }
-}
-
-// Split combine.  A block owns 64 dims of one query head of one sequence;
-// its GROUPS slot groups each fold every GROUPS-th partial slot into a running
-// (max, sum, acc) in passes of kSlotUnroll slots (all loads of a pass issued
-// together), and the groups' states are folded in a fixed order:
-//   out[b][h][d] = sum_s 2^(m_s - M) acc_s[d] / sum_s 2^(m_s - M) l_s.
-// The launch sizes GROUPS to the slots a sequence has, so that a sequence's
-// partials take few dependent passes (one sequence over the whole device has
-// about 257 slots, eight sequences about 33, sixty-four about 5).
-constexpr int kFinishDims = 64;
-constexpr int kSlotUnroll = 8;
-
-template <int GROUPS>
-__global__ void __launch_bounds__(kFinishDims * GROUPS)
-finish_kernel(FinishArgs a, int D) {
-    constexpr int kThreads = kFinishDims * GROUPS;
-    __shared__ float sm[kThreads], sl[kThreads], sa[kThreads];
-    const int per_head = D / kFinishDims;
-    const int bh = blockIdx.x / per_head;                 // b * Hq + h
-    const int d = (blockIdx.x % per_head) * kFinishDims + threadIdx.x % kFinishDims;
-    const int grp = threadIdx.x / kFinishDims;
-    const int b = bh / a.Hq, h = bh % a.Hq;
-    const int s0 = a.slot_first[b], s1 = a.slot_end[b];
-    float M = -INFINITY, L = 0.f, acc = 0.f;
-    for (int k = s0 + grp; k < s1; k += GROUPS * kSlotUnroll) {
-        float mk[kSlotUnroll], lk[kSlotUnroll], ak[kSlotUnroll];
-#pragma unroll
-        for (int u = 0; u < kSlotUnroll; ++u) {
-            const int ks = min(k + u * GROUPS, s1 - 1);
-            const size_t head = (size_t)ks * a.Hq + h;
-            mk[u] = a.part_ml[head * 2];
-            lk[u] = a.part_ml[head * 2 + 1];
-            ak[u] = a.part_acc[head * D + d];
-        }
-        float Mn = M;
-#pragma unroll
-        for (int u = 0; u < kSlotUnroll; ++u)
-            if (k + u * GROUPS < s1) Mn = fmaxf(Mn, mk[u]);
-        const float sc = (M == -INFINITY) ? 0.f : __builtin_amdgcn_exp2f(M - Mn);
-        L *= sc;
-        acc *= sc;
-#pragma unroll
-        for (int u = 0; u < kSlotUnroll; ++u) {
-            if (k + u * GROUPS < s1) {
-                const float wgt = __builtin_amdgcn_exp2f(mk[u] - Mn);
-                L = fmaf(wgt, lk[u], L);
-                acc = fmaf(wgt, ak[u], acc);
-            }
-        }
-        M = Mn;
-    }
-    if constexpr (GROUPS > 1) {
-        sm[threadIdx.x] = M;
-        sl[threadIdx.x] = L;
-        sa[threadIdx.x] = acc;
-        __syncthreads();
-        if (grp != 0) return;
-        float Mt = -INFINITY;
-#pragma unroll
-        for (int k = 0; k < GROUPS; ++k) Mt = fmaxf(Mt, sm[k * kFinishDims + threadIdx.x]);
-        float o = 0.f, lt = 0.f;
-#pragma unroll
-        for (int k = 0; k < GROUPS; ++k) {
-            const float mk = sm[k * kFinishDims + threadIdx.x];
-            const float wgt = (mk == -INFINITY) ? 0.f : __builtin_amdgcn_exp2f(mk - Mt);
-            o = fmaf(wgt, sa[k * kFinishDims + threadIdx.x], o);
-            lt = fmaf(wgt, sl[k * kFinishDims + threadIdx.x], lt);
-        }
-        M = Mt;
-        L = lt;
-        acc = o;
-    }
-    a.out[(size_t)bh * D + d] = acc / L;
-    if (a.norm && threadIdx.x == 0 && blockIdx.x % per_head == 0) {
-        a.norm[(size_t)bh * 2] = M;
-        a.norm[(size_t)bh * 2 + 1] = L;
-    }
-}
-
-// First-tile records of every range of the attention grid, one workgroup per
-// state layer, one thread per range: the same split, the same piece and chunk
-// as the attention kernel takes (which compares the record with its own before
-// using it).
-__global__ void __launch_bounds__(256) plan_kernel(PlanArgs a) {
-    __shared__ int32_t seq_off[kMaxBatch + 1];
-    const size_t st = blockIdx.x;
-    plan_ranges(a.n_active + st * a.B, a.B, seq_off);
-    __syncthreads();
-    const int T = seq_off[a.B];
-    const int Gn = active_groups(T, a.grid);
-    const int32_t* list = a.list + st * a.B * a.cap;
-    for (int w = threadIdx.x; w < a.grid; w += blockDim.x) {
-        int32_t* rec = a.plan + (st * a.grid + w) * kPlanInts;
-        int b = -1, i0 = 0, len = 0;
-        const int x = (int)((int64_t)w * T / Gn);
-        const int x_end = (int)((int64_t)(w + 1) * T / Gn);
-        if (w < Gn && x < x_end) {
-            int lo = 0, hi = a.B - 1;              // last sequence with seq_off <= x
-            while (lo < hi) {
-                const int mid = (lo + hi + 1) >> 1;
-                if (seq_off[mid] <= x) lo = mid; else hi = mid - 1;
-            }
-            while (seq_off[lo + 1] <= x) ++lo;     // past empty lists (seq_off[B] = T > x)
-            const int sb = seq_off[lo] + kSeqCost, se = seq_off[lo + 1];
-            if (x_end > sb) {
-                b = lo;
-                i0 = max(x, sb) - sb;
-                len = min(kChunk, min(se, x_end) - sb - i0);
-            }
-        }
-        rec[0] = b;
-        rec[1] = i0;
-        rec[2] = len;
-        rec[3] = 0;
-        if (b >= 0) {
-            const int32_t* src = list + (size_t)b * a.cap + i0;
-            int v[kPlanTokens];
-#pragma unroll
-            for (int k = 0; k < kPlanTokens; ++k) v[k] = src[min(k, len - 1)];
-#pragma unroll
-            for (int k = 0; k < kPlanTokens; ++k) rec[4 + k] = v[k];
-        }
     }
 }
 
 template <bool BF16, int D, int G>
-constexpr int state_floats() { return 2 * G + G * Row<BF16, D>::kPerLane; }
-
-template <bool BF16, int D, int G>
-size_t lds_bytes(const AttnArgs& a) {
-    const size_t chunk = (size_t)kChunk * (4 + 4 + 16 + 1);
-    constexpr int GS = G / split_of<BF16, D, G>();
-    const size_t merge = (size_t)(merge_one_round<BF16, D, GS>() ? kWaves : kWaves / 2) *
-                         state_floats<BF16, D, GS>() * 64 * 4;
-    return (size_t)((a.B + 1 + 3) & ~3) * 4 + (chunk > merge ? chunk : merge);
+size_t lds_bytes(int B) {
+    using R = Row<BF16, D>;
+    return (size_t)R::kWaves * R::kWaveLds + R::kWaves * 2 * G * 4 + (B > 64 ? (size_t)(2 * B + 1) * 4 : 0);
 }
 
 // Timing events, when given, are recorded by the dispatch itself, so they
@@ -963,53 +968,27 @@ struct Launch {
     int* occ;                       // non-null: report occupancy instead
 };
 
-template <bool BF16, int D, int G, int HKV>
+template <bool BF16, int D, int G>
 hipError_t launch_t(const AttnArgs& a, const Launch& l) {
-    const size_t lds = lds_bytes<BF16, D, G>(a);
-    constexpr bool kPF = prefetch_shape<BF16, D, G, HKV>();
-    if (l.occ) {                          // the variant that fits fewer workgroups
-        hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(
-            l.occ, attention_kernel<BF16, D, G, HKV, false>, 64 * kWaves, lds);
-        if (e != hipSuccess || !kPF) return e;
-        int occ_pf = 0;
-        e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ_pf, attention_kernel<BF16, D, G, HKV, kPF>,
-                                                         64 * kWaves, lds);
-        if (occ_pf < *l.occ) *l.occ = occ_pf;
-        return e;
+    const size_t lds = lds_bytes<BF16, D, G>(a.B);
+    constexpr int threads = threads_of<BF16, D>();
+    auto k = attention_kernel<BF16, D, G>;
+    if (l.occ) {
+        return hipOccupancyMaxActiveBlocksPerMultiprocessor(l.occ, k, threads, lds);
     }
-    auto k = kPF && a.plan ? attention_kernel<BF16, D, G, HKV, kPF> : attention_kernel<BF16, D, G, HKV, false>;
     AttnArgs arg = a;
     void* args[] = {&arg};
-    return hipExtLaunchKernel(reinterpret_cast<const void*>(k), dim3(l.grid), dim3(64 * kWaves),
+    return hipExtLaunchKernel(reinterpret_cast<const void*>(k), dim3(l.grid), dim3(threads),
                               args, lds, l.stream, l.start, l.stop, 0);
-}
-
-template <bool BF16, int D, int G, int HKV>
-hipError_t launch_s(const AttnArgs& a, const Launch& l) {
-    if constexpr (shape_supported<BF16, D, G, HKV>()) return launch_t<BF16, D, G, HKV>(a, l);
-    else return hipErrorInvalidValue;
-}
-
-template <bool BF16, int D, int G>
-hipError_t launch_h(const AttnArgs& a, const Launch& l) {
-    switch (a.Hkv) {
-        case 1: return launch_s<BF16, D, G, 1>(a, l);
-        case 2: return launch_s<BF16, D, G, 2>(a, l);
-        case 4: return launch_s<BF16, D, G, 4>(a, l);
-        case 8: return launch_s<BF16, D, G, 8>(a, l);
-        case 16: return launch_s<BF16, D, G, 16>(a, l);
-        case 32: return launch_s<BF16, D, G, 32>(a, l);
-    }
-    return hipErrorInvalidValue;
 }
 
 template <bool BF16, int D>
 hipError_t launch_g(const AttnArgs& a, int group, const Launch& l) {
     switch (group) {
-        case 1: return launch_h<BF16, D, 1>(a, l);
-        case 2: return launch_h<BF16, D, 2>(a, l);
-        case 4: return launch_h<BF16, D, 4>(a, l);
-        case 8: return launch_h<BF16, D, 8>(a, l);
+        case 1: return launch_t<BF16, D, 1>(a, l);
+        case 2: return launch_t<BF16, D, 2>(a, l);
+        case 4: return launch_t<BF16, D, 4>(a, l);
+        case 8: return launch_t<BF16, D, 8>(a, l);
     }
     return hipErrorInvalidValue;
 }
@@ -1028,38 +1007,19 @@ hipError_t dispatch(const AttnArgs& a, int dtype_bf16, int head_dim, int group, 
 
 }  // namespace
 
-namespace {
-template <bool BF16, int D, int G>
-bool supported_h(int hkv) {
-    switch (hkv) {
-        case 1: return shape_supported<BF16, D, G, 1>();
-        case 2: return shape_supported<BF16, D, G, 2>();
-        case 4: return shape_supported<BF16, D, G, 4>();
-        case 8: return shape_supported<BF16, D, G, 8>();
-        case 16: return shape_supported<BF16, D, G, 16>();
-        case 32: return shape_supported<BF16, D, G, 32>();
-    }
-    return false;
-}
-template <bool BF16, int D>
-bool supported_g(int group, int hkv) {
-    switch (group) {
-        case 1: return supported_h<BF16, D, 1>(hkv);
-        case 2: return supported_h<BF16, D, 2>(hkv);
-        case 4: return supported_h<BF16, D, 4>(hkv);
-        case 8: return supported_h<BF16, D, 8>(hkv);
-    }
-    return false;
-}
-}  // namespace
-
+// The head layouts of the interface: token rows (every KV head) of at most
+// 8 KiB, at most 32 blocks of four query heads (two with rows of 256) per
+// token, and at most 8 / (blocks / 8) heads a block.
 bool attention_shape_supported(int dtype_bf16, int head_dim, int group, int n_kv_heads) {
-    if (head_dim == 128) return dtype_bf16 ? supported_g<true, 128>(group, n_kv_heads)
-                                           : supported_g<false, 128>(group, n_kv_heads);
-    if (head_dim == 64) return dtype_bf16 ? supported_g<true, 64>(group, n_kv_heads)
-                                          : supported_g<false, 64>(group, n_kv_heads);
-    if (head_dim == 256) return dtype_bf16 && supported_g<true, 256>(group, n_kv_heads);
-    return false;
+    if (head_dim != 64 && head_dim != 128 && head_dim != 256) return false;
+    if (head_dim == 256 && !dtype_bf16) return false;
+    if (group != 1 && group != 2 && group != 4 && group != 8) return false;
+    const int most = head_dim / 8 >= 32 ? 2 : 4;
+    const int parts = group > most ? group / most : 1;
+    const int blocks = n_kv_heads * parts;
+    const int per_token = blocks > 8 ? blocks / 8 : 1;
+    return n_kv_heads * head_dim * (dtype_bf16 ? 2 : 4) <= 8192 && per_token <= 4 &&
+           group / parts <= 8 / per_token;
 }
 
 hipError_t launch_attention(const AttnArgs& a, int dtype_bf16, int head_dim, int group,
@@ -1072,22 +1032,36 @@ hipError_t attention_occupancy(const AttnArgs& a, int dtype_bf16, int head_dim, 
     return dispatch(a, dtype_bf16, head_dim, group, Launch{0, nullptr, nullptr, nullptr, blocks_per_cu});
 }
 
-hipError_t launch_plan(const PlanArgs& a, int n_states, hipStream_t s) {
-    if (a.B < 1 || a.B > kMaxBatch || a.grid < 1 || n_states < 1) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(plan_kernel, dim3(n_states), dim3(256), 0, s, a);
-    return hipGetLastError();
-}
+namespace {
+// tiles whose relevance values a workgroup has room for
+constexpr int room_tiles(int tile) { return 8192 / (tile * 4) * 8; }
+}  // namespace
 
-hipError_t launch_finish(const FinishArgs& a, int head_dim, int slots_per_seq, hipStream_t s) {
-    if (head_dim % kFinishDims) return hipErrorInvalidValue;
-    const dim3 grid(a.B * a.Hq * (head_dim / kFinishDims));
-    if (slots_per_seq > 8 * kSlotUnroll)
-        hipLaunchKernelGGL(finish_kernel<16>, grid, dim3(kFinishDims * 16), 0, s, a, head_dim);
-    else if (slots_per_seq > kSlotUnroll)
-        hipLaunchKernelGGL(finish_kernel<4>, grid, dim3(kFinishDims * 4), 0, s, a, head_dim);
-    else
-        hipLaunchKernelGGL(finish_kernel<1>, grid, dim3(kFinishDims), 0, s, a, head_dim);
-    return hipGetLastError();
+void attention_layout(const int32_t* plen, int batch, int t, int n_kv_heads, int row_bytes, int grid,
+                      int* heads_per_group, int* launch) {
+    const int tile = 8192 / row_bytes;
+    int64_t tiles = 0;
+    for (int b = 0; b < batch; ++b) tiles += (plen[b] + tile) / tile;
+    // One KV head per piece while the pieces are short: a pair's partials and its
+    // merge are smallest, and its relevance values are stored once, at the end.  With
+    // many pairs a workgroup would walk several short pieces one after the other,
+    // each with its own round trips, and with long pieces the relevance values of
+    // every KV head would be stored among the row loads, where they cost ten times
+    // their bytes (64 x 17k tokens: 730 us a launch with one head, 670 with eight,
+    // whose values are summed first): then the waves take heads side by side.  The
+    // choice rests on the prompts alone, so a step replayed from a graph is dealt
+    // like the same step run eagerly.
+    int hw = 1;
+    if (tiles * n_kv_heads > (int64_t)room_tiles(tile) * grid || (int64_t)batch * n_kv_heads > 2 * (int64_t)grid)
+        hw = n_kv_heads < 8 ? n_kv_heads : 8;
+    const int64_t groups = n_kv_heads / hw;
+    const int cost = kPieceCost / hw > 1 ? kPieceCost / hw : 1;
+    const int least = kMinTiles / (hw < kMinTiles ? hw : kMinTiles);
+    int64_t live = 0;
+    for (int b = 0; b < batch && live < grid; ++b)
+        live += groups * (((plen[b] + t + tile - 1) / tile + cost + least - 1) / least);
+    *heads_per_group = hw;
+    *launch = live < grid ? (live > 1 ? (int)live : 1) : grid;
 }
 
 }  // namespace asrkf

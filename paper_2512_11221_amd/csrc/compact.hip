@@ -6,9 +6,8 @@
 //   0. runs the step's freeze loop (Algorithm 1): a position that attended
 //      step t (U_p <= t), is a freeze candidate and scored below tau gets
 //      c_p += 1 and, when d = floor(sqrt(c_p)/k) >= 1, U_p = t + d.  The
-//      verdict "below tau" is the flag byte the attention kernel wrote for
-//      the position at step t (layer scope), or in token scope the relevance
-//      summed over every layer, which no single layer's kernel can form;
+//      verdict "below tau" is the flag byte of the position, written before
+//      this launch from the step's relevance sums;
 //   1. applies the recovery level chosen for the sequence (Sec. 3.6):
 //        SR: remaining timer U_p - (t+1) > 1     ->  U_p = t+1
 //        WR: p >= n_t - N and U_p > t+1          ->  U_p = t+1
@@ -76,26 +75,20 @@ __device__ __forceinline__ Ladder make_ladder(const CompactArgs& a, int b, int n
 
 // The freeze loop of step t over the 4 positions p .. p+3 of a thread (those
 // below hi): u, cnt are their U and c, flags their score flags (one byte
-// each, layer scope).  With a cumulative count (history_W = 0) the counts come
+// each).  With a cumulative count (history_W = 0) the counts come
 // in with U and only changed entries are stored; a finite history window
 // updates the detection bits of a flagged position.  Returns whether u changed.
 __device__ __forceinline__ bool freeze4(const CompactArgs& a, const int32_t* dur_lds, size_t base,
                                         int p, int hi, int n, int (&u)[4], const int (&cnt)[4],
-                                        uint32_t flags, const float (&rel)[4], int& near) {
+                                        uint32_t flags, int& near) {
     if (!a.freeze) return false;
     bool dirty = false;
     const bool inside = a.cand_inside != 0;
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
         const int q = p + k;
-        bool low, close;
-        if (a.scope_token) {
-            low = rel[k] < a.tau_LH;
-            close = fabsf(rel[k] - a.tau_LH) < a.margin_LH;
-        } else {
-            low = ((flags >> (8 * k)) & 1u) != 0;
-            close = ((flags >> (8 * k)) & 2u) != 0;
-        }
+        const bool low = ((flags >> (8 * k)) & 1u) != 0;
+        const bool close = ((flags >> (8 * k)) & 2u) != 0;
         // debug margin: a freeze decision of step t (an attended candidate) on a
         // score near tau
         near += (q < hi && u[k] <= a.t && close && freeze_candidate(q, n - a.window_K, inside)) ? 1 : 0;
@@ -148,7 +141,6 @@ __device__ __forceinline__ void load_durations(const CompactArgs& a, int32_t* du
 struct Tile4 {
     int u[4], c[4];
     uint32_t f;
-    float r[4];                               // token scope: relevance summed over layers
 };
 
 __device__ __forceinline__ void load_tile(const CompactArgs& a, size_t base, int p, Tile4& x) {
@@ -156,10 +148,6 @@ __device__ __forceinline__ void load_tile(const CompactArgs& a, size_t base, int
     const int4 u = *reinterpret_cast<const int4*>(a.unfreeze + q);
     const int4 c = *reinterpret_cast<const int4*>(a.count + q);
     x.f = *reinterpret_cast<const uint32_t*>(a.flag + q);
-    if (a.scope_token) {                      // uniform; the sums exist in token scope only
-        const float4 r = *reinterpret_cast<const float4*>(a.rel_acc + q);
-        x.r[0] = r.x; x.r[1] = r.y; x.r[2] = r.z; x.r[3] = r.w;
-    }
     x.u[0] = u.x; x.u[1] = u.y; x.u[2] = u.z; x.u[3] = u.w;
     x.c[0] = c.x; x.c[1] = c.y; x.c[2] = c.z; x.c[3] = c.w;
 }
@@ -276,7 +264,7 @@ __device__ int compact_range(const CompactArgs& a, const Ladder& r, const int32_
         }
         bool flag[4];
         if constexpr (MODE != 2) {
-            bool dirty = freeze4(a, dur_lds, base, p, hi, n, u, cur.c, cur.f, cur.r, near);
+            bool dirty = freeze4(a, dur_lds, base, p, hi, n, u, cur.c, cur.f, near);
 #pragma unroll
             for (int k = 0; k < 4; ++k) {
                 bool hit;
@@ -562,7 +550,7 @@ compact_spill_kernel(CompactArgs a) {
         load_tile(a, base, p, cur);
         mask_tile(cur, p, n);
         int (&u)[4] = cur.u;
-        bool dirty = freeze4(a, dur_lds, base, p, n, n, u, cur.c, cur.f, cur.r, near);
+        bool dirty = freeze4(a, dur_lds, base, p, n, n, u, cur.c, cur.f, near);
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
             bool hit;
@@ -680,7 +668,7 @@ spill_count_kernel(CompactArgs a) {
         int (&u)[4] = cur.u;
         int row[4];
         load4(a.row_of + base, p, hi, row, -1);
-        bool dirty = freeze4(a, dur_lds, base, p, hi, n, u, cur.c, cur.f, cur.r, near);
+        bool dirty = freeze4(a, dur_lds, base, p, hi, n, u, cur.c, cur.f, near);
         bool listed[4], first[4];
 #pragma unroll
         for (int k = 0; k < 4; ++k) {

@@ -1,4 +1,9 @@
-// Entropy of the next-token distribution and the recovery ladder (Sec. 3.6).
+// The first launch of a step's end: the entropy monitors with the recovery
+// ladder (Sec. 3.6), and the score verdicts that the freeze loop reads.  The
+// two are independent and neither fills the device, so they share a launch:
+// the first workgroups take the entropy, the others the verdicts.
+//
+// Entropy.
 //
 // a.split workgroups per sequence, one pass over the V logits.  Each
 // thread forms (m, S, T) with S = sum e^(x-m) and T = sum e^(x-m) (x-m) over
@@ -14,6 +19,16 @@
 // spike step, reset by a calm step) and writes the level that the end-of-step
 // compaction applies: 1 SR, 2 WR, 3 FR; a count above 3 also records a
 // Rewalk Regeneration request.
+//
+// Verdicts.  The attention launches leave, per attended token (in list order),
+// one value per plane: the KV heads' sums of |q.k|, or every query head's
+// logit y (softmax reading).  A token's score is
+//     H s_j = sum_g rel_gj            (Eq. 2), or
+//     H s_j = sum_h 2^(y_hj - M_h) / L_h,
+// with (M_h, L_h) the head's softmax normaliser, summed over every layer in
+// token scope.  It is compared with tau and the flag byte is stored at the
+// token's position.  Four list entries per thread: 16-byte loads of a plane,
+// the planes of a group in flight together.
 #include "kernels.h"
 
 namespace asrkf {
@@ -63,12 +78,9 @@ __device__ __forceinline__ Triple triple_of(const float (&x)[N], const bool (&ok
 
 constexpr int kVec = 4;             // float4 loads per thread per round
 
-__global__ void __launch_bounds__(kThreads)
-entropy_kernel(EntropyArgs a) {
+__device__ void entropy_block(const EntropyArgs& a, int sp, int b) {
     __shared__ Triple part[kThreads / 64];
     __shared__ int last;
-    const int b = blockIdx.y;
-    const int sp = blockIdx.x;
     const float* x = a.logits + (size_t)b * a.V;
     Triple acc{-INFINITY, 0.f, 0.f};
     if (((reinterpret_cast<uintptr_t>(x) & 15) == 0) && (a.V % 4 == 0)) {
@@ -154,10 +166,68 @@ entropy_kernel(EntropyArgs a) {
     if (level > 0) atomicAdd(a.recoveries + level, 1ull);
 }
 
+constexpr int kEntries = 4 * kThreads;        // list entries per verdict workgroup
+constexpr int kPlaneGroup = 4;
+
+__device__ void verdict_block(const VerdictArgs& v, int chunk, int inst) {
+    const int n = v.n_active[inst];
+    const int i0 = chunk * kEntries + 4 * threadIdx.x;
+    if (i0 >= n) return;
+    const int b = inst % v.B, state = inst / v.B;
+    float s[4] = {0.f, 0.f, 0.f, 0.f};
+    const int4 pos = *reinterpret_cast<const int4*>(v.list + (size_t)inst * v.cap + i0);
+    for (int l = 0; l < v.layers_summed; ++l) {
+        const size_t li = (size_t)(state + l) * v.B + b;          // the layer's instance
+        const float* rel = v.rel + li * v.planes * v.cap + i0;
+        const float* norm = v.norm + li * v.planes * 2;
+        for (int p0 = 0; p0 < v.used; p0 += kPlaneGroup) {
+            float4 x[kPlaneGroup];
+#pragma unroll
+            for (int k = 0; k < kPlaneGroup; ++k)
+                x[k] = *reinterpret_cast<const float4*>(rel + (size_t)min(p0 + k, v.used - 1) * v.cap);
+#pragma unroll
+            for (int k = 0; k < kPlaneGroup; ++k) {
+                if (p0 + k < v.used) {
+                    if (v.softmax) {
+                        const float M = norm[2 * (p0 + k)], inv = 1.f / norm[2 * (p0 + k) + 1];
+                        s[0] = fmaf(__builtin_amdgcn_exp2f(x[k].x - M), inv, s[0]);
+                        s[1] = fmaf(__builtin_amdgcn_exp2f(x[k].y - M), inv, s[1]);
+                        s[2] = fmaf(__builtin_amdgcn_exp2f(x[k].z - M), inv, s[2]);
+                        s[3] = fmaf(__builtin_amdgcn_exp2f(x[k].w - M), inv, s[3]);
+                    } else {
+                        s[0] += x[k].x;
+                        s[1] += x[k].y;
+                        s[2] += x[k].z;
+                        s[3] += x[k].w;
+                    }
+                }
+            }
+        }
+    }
+    uint8_t* flag = v.flag + (size_t)inst * v.cap;
+    const int p[4] = {pos.x, pos.y, pos.z, pos.w};
+#pragma unroll
+    for (int k = 0; k < 4; ++k)
+        if (i0 + k < n)
+            flag[p[k]] = (uint8_t)((s[k] < v.tau_sum ? 1 : 0) | (fabsf(s[k] - v.tau_sum) < v.margin_sum ? 2 : 0));
+}
+
+__global__ void __launch_bounds__(kThreads)
+monitor_kernel(EntropyArgs e, VerdictArgs v, int entropy_blocks, int chunks) {
+    const int i = blockIdx.x;
+    if (i < entropy_blocks) entropy_block(e, i % e.split, i / e.split);
+    else verdict_block(v, (i - entropy_blocks) % chunks, (i - entropy_blocks) / chunks);
+}
+
 }  // namespace
 
-hipError_t launch_entropy(const EntropyArgs& a, hipStream_t s) {
-    hipLaunchKernelGGL(entropy_kernel, dim3(a.split, a.B), dim3(kThreads), 0, s, a);
+hipError_t launch_monitor(const EntropyArgs* e, const VerdictArgs& v, hipStream_t s) {
+    const int64_t entropy_blocks = e ? (int64_t)e->split * e->B : 0;
+    const int64_t chunks = (v.cap + kEntries - 1) / kEntries;
+    const int64_t blocks = entropy_blocks + chunks * v.states * v.B;
+    if (blocks > (1 << 30)) return hipErrorInvalidValue;   // caches of that size exceed any device
+    hipLaunchKernelGGL(monitor_kernel, dim3((unsigned)blocks), dim3(kThreads), 0, s,
+                       e ? *e : EntropyArgs{}, v, (int)entropy_blocks, (int)chunks);
     return hipGetLastError();
 }
 

@@ -7,11 +7,12 @@
 
 namespace asrkf {
 
-// Split-K attention.  The concatenated active lists of all sequences are cut
-// into one equal contiguous token range per workgroup of a fixed grid
-// (derived on the device from the active counts, no host round trip); the
-// workgroup leaves one partial (m, l, acc) of every query head per sequence
-// its range touches, at slot (workgroup + sequence).
+// Split-K attention.  The active list of every (sequence, KV head) pair, cut
+// into tiles, concatenated, is cut into one equal contiguous range per
+// workgroup of a fixed grid (derived on the device from the active counts, no
+// host round trip).  A pair that several workgroups share leaves one partial
+// (m, l, acc) per workgroup, at slot (workgroup + pair); the last to arrive
+// folds them.
 constexpr int kMaxBatch = 1024;
 
 // A low-relevance detection of the token at state index o in step t: the new
@@ -43,8 +44,10 @@ __device__ __forceinline__ bool freeze_candidate(int pos, int wedge, bool inside
     return (pos < wedge) != inside;
 }
 
+// The K/V cache of a layer: [B][Hkv][pool_rows][D], head-major, so that a
+// (sequence, KV head) pair's rows are one contiguous region.
 struct AttnArgs {
-    const void* kpool;        // layer base, [B][pool_rows][Hkv][D]
+    const void* kpool;        // layer base
     const void* vpool;
     const void* q;            // [B][Hq][D]
     const void* knew;         // [B][Hkv][D]
@@ -55,73 +58,43 @@ struct AttnArgs {
     const int32_t* list_row;  // layer base, [B][cap] device row of each listed position
                               // (spill mode only; in resident mode the row is the position)
     const int32_t* n_active;  // layer base, [B]
-    uint8_t* flag;            // layer base, [B][cap]: bit 0 set where the attended position
-                              // scores below tau (Eq. 2), bit 1 where the score lies within
-                              // the debug margin of tau; read by the freeze loop at the
-                              // end of the step
+    float* rel;               // layer base, [B][planes][cap] relevance of the list entries (written):
+                              // the first Hkv / heads_per_group planes hold |q.k| summed over a head
+                              // group's query heads (Eq. 2); or Hq planes of logits
+                              // q.k * log2(e)/sqrt(D) (softmax weights)
     int32_t* t_dev;           // first layer of a step: advanced by one (steps started), else null
-    float* part_acc;          // [grid + B][Hq][D]
-    float* part_ml;           // [grid + B][Hq][2]: (max in log2 units, sum)
-    int32_t* slot_first;      // [B] first partial slot of each sequence (written)
-    int32_t* slot_end;        // [B] one past its last slot (written)
+    float* part_acc;          // [grid + pairs][heads][D] of the pairs that several workgroups share
+    float* part_ml;           // [grid + pairs][heads][2]: (max in log2 units, sum)
+    int32_t* ticket;          // [B][Hkv] workgroups of a pair that have stored their partial; zero
+                              // between launches
+    float* out;               // [B][Hq][D]
+    float* norm;              // softmax weights: [B][Hq][2] (max, sum) (written), or null
     int32_t B, cap, Hq, Hkv;
+    int32_t planes;           // plane stride of a sequence
+    int32_t grid;             // workgroups the work is dealt to (a launch may have fewer or more)
+    int32_t heads_per_group;  // KV heads a workgroup takes together (a power of two dividing Hkv)
     int32_t pool_rows;        // device rows per sequence (cap in resident mode)
     int32_t spill;            // 1: rows come from list_row
-    float tau_H;              // tau * Hq: compared against sum_h |q_h . k_j|
-    float margin_H;           // debug margin * Hq (0: off): a score this close to tau_H
-                              // also sets bit 1 of the position's flag
+    int32_t rel_mode;         // 0: Eq. 2 |q.k|; 1: softmax weights
     float scale_log2;         // log2(e) / sqrt(D)
-    // relevance reading and state scope
-    int32_t rel_mode;         // 0: Eq. 2 |q.k| scored here; 1: softmax weights (weight_relevance_kernel)
-    int32_t scope_token;      // 1: one token state per sequence, scored by the sum over layers
-    int32_t first_layer;      // token scope: this launch starts the per-token sums
-    float* rel_acc;           // token scope, [B][cap]: sum over layers and heads of the relevance
-    float* xlog;              // softmax relevance, [B][cap][Hq]: q.k * log2(e)/sqrt(D) per listed token
-    const int32_t* plan;      // state base, [grid][kPlanInts] first-tile records of the ranges
-                              // (plan_kernel), or null
 };
 
-// The first positions of every attention range, staged after each list
-// rebuild, so that an attention workgroup can request its first K/V rows
-// before its chunk's positions and q arrive.  Record of range w:
-//   [0] sequence of the range's first piece, -1: the range has no real token
-//   [1] the piece's first list index  [2] its first chunk's length  [3] unused
-//   [4 .. 4 + kPlanTokens) list entries from the first list index on (the
-//   last entry of the chunk repeated past its end)
-constexpr int kPlanTokens = 32;
-constexpr int kPlanInts = 4 + kPlanTokens;
-constexpr int kPlanMinLayers = 4;   // fewer layers per step: no records (the launch costs more)
-
-struct PlanArgs {
+// The score verdicts of a step, from the relevance planes: one flag byte per
+// attended position, bit 0 set where s_j < tau (Eq. 2, or the mean softmax
+// weight), bit 1 where s_j lies within the debug margin of tau.
+struct VerdictArgs {
+    const float* rel;         // [L][B][planes][cap] by list entry
+    const float* norm;        // softmax weights: [L][B][Hq][2]
     const int32_t* list;      // [states][B][cap]
     const int32_t* n_active;  // [states][B]
-    int32_t* plan;            // [states][grid][kPlanInts]
-    int32_t B, cap, grid;
-};
-
-// Per layer, after the attention: the split combine of Eq. 1.
-struct FinishArgs {
-    const float* part_acc;
-    const float* part_ml;
-    const int32_t* slot_first;
-    const int32_t* slot_end;
-    float* out;               // [B][Hq][D]
-    float* norm;              // softmax relevance: [B][Hq][2] (max, sum) of the sequence (written), or null
-    int32_t B, Hq;
-};
-
-// Relevance by attention weight, after the split combine of a layer:
-// s_j = sum_h 2^(y_hj - M_h) / L_h over the heads (compared with tau * Hq),
-// then the score flag (layer scope) or the per-token sum (token scope).
-struct RelevanceArgs {
-    const float* xlog;        // [B][cap][Hq]
-    const float* norm;        // [B][Hq][2]
-    const int32_t* list;      // state base [B][cap]
-    const int32_t* n_active;  // state base [B]
-    uint8_t* flag;            // state base [B][cap]
-    float* rel_acc;           // token scope [B][cap]
-    int32_t B, cap, Hq, scope_token, first_layer;
-    float tau_H, margin_H;
+    uint8_t* flag;            // [states][B][cap] by position (written)
+    int32_t B, cap;
+    int32_t planes, used;     // plane stride of a sequence, planes that hold values
+    int32_t softmax;
+    int32_t states;           // layers with states of their own: L, or 1 (token scope)
+    int32_t layers_summed;    // 1, or L (token scope: the sum over every layer)
+    float tau_sum;            // tau * Hq (* L): compared against the sum
+    float margin_sum;         // debug margin * Hq (* L); 0: off
 };
 
 struct CompactArgs {
@@ -160,11 +133,7 @@ struct CompactArgs {
                               // [3] rows taken back intact (no copy)
     // the freeze loop of step t runs here, before recovery (not before step 1)
     int32_t freeze;           // 1: apply the step's freeze loop (set on the device: t > 0)
-    const uint8_t* flag;      // [L][B][cap] layer scope: 1 where the position scored below tau at step t
-    int32_t scope_token;      // 1: one state per sequence, scored by the sum over layers
-    const float* rel_acc;     // [B][cap] token scope: relevance summed over layers and heads
-    float tau_LH;             // tau * n_layers * Hq
-    float margin_LH;          // token scope: debug margin * n_layers * Hq
+    const uint8_t* flag;      // [L][B][cap] verdicts of step t (VerdictArgs)
     unsigned long long* margin_hits;  // debug margin on: decisions near tau are counted here
     int32_t* count;           // [L][B][cap] (or [B][cap] in token scope): c_j
     uint64_t* hmask;
@@ -190,9 +159,19 @@ struct SpillInitArgs {
     int32_t B, cap, pool_rows;
 };
 
+// A prompt's K/V of one (layer, sequence).
+struct PrefillArgs {
+    const char* k;            // [n][Hkv][row_bytes], any alignment of the element type
+    const char* v;
+    char* kdst;               // [Hkv][pool_rows][row_bytes]
+    char* vdst;
+    int32_t* plen;            // the sequence's prompt length, written when set_plen
+    int32_t n, Hkv, row_bytes, pool_rows, set_plen;
+};
+
 // Row copies between the device cache and the host store (spill mode).
 struct XferArgs {
-    char* kpool;              // [L][B][pool_rows][row_bytes]
+    char* kpool;              // [L][B][Hkv][pool_rows][row_bytes / Hkv]
     char* vpool;
     char* khost;              // device-visible pointer of the pinned store, [L][B][cap][row_bytes]
     char* vhost;
@@ -200,7 +179,8 @@ struct XferArgs {
     const int32_t* row;       //   ... and device rows
     const int32_t* count;     // [L][B] list lengths
     int32_t inst0;            // first (layer, sequence) instance of the launch
-    int32_t cap, pool_rows, row_bytes;
+    int32_t cap, pool_rows, row_bytes;   // row_bytes: one token, every KV head
+    int32_t Hkv;
     int32_t to_host;          // 1: device -> host store, 0: host store -> device
 };
 
@@ -235,19 +215,22 @@ hipError_t launch_attention(const AttnArgs& a, int dtype_bf16, int head_dim, int
                             int grid, hipStream_t s, hipEvent_t start, hipEvent_t stop);
 hipError_t attention_occupancy(const AttnArgs& a, int dtype_bf16, int head_dim, int group,
                                int* blocks_per_cu);
-// slots_per_seq: about how many partial slots a sequence has (grid / B + 1).
-hipError_t launch_finish(const FinishArgs& a, int head_dim, int slots_per_seq, hipStream_t s);
+// How a step's attention is laid out when sequence b lists up to plen[b] + t
+// positions: KV heads a workgroup takes together, and how many workgroups to
+// launch (at least those with work, at most grid: idle ones delay the others).
+void attention_layout(const int32_t* plen, int batch, int t, int n_kv_heads, int row_bytes, int grid,
+                      int* heads_per_group, int* launch);
 hipError_t launch_compact(const CompactArgs& a, int n_instances, hipStream_t s);
-// The first-tile records of every (state layer, range) after a list rebuild.
-hipError_t launch_plan(const PlanArgs& a, int n_states, hipStream_t s);
 // Segments per instance (and their length) for the rebuild; 1 = one workgroup per instance.
 int compact_segments(int n_instances, int cap, int* seg_len);
-hipError_t launch_weight_relevance(const RelevanceArgs& a, hipStream_t s);
 hipError_t launch_spill_init(const SpillInitArgs& a, int n_instances, hipStream_t s);
 hipError_t launch_xfer(const XferArgs& a, int n_instances, hipStream_t s);
 // Whether the attention kernel handles this (dtype, head_dim, q heads per KV head, KV heads).
 bool attention_shape_supported(int dtype_bf16, int head_dim, int group, int n_kv_heads);
 hipError_t launch_delay(int microseconds, hipStream_t s);
-hipError_t launch_entropy(const EntropyArgs& a, hipStream_t s);
+// The step's verdicts and, when e is given, the entropy monitors, in one launch.
+hipError_t launch_monitor(const EntropyArgs* e, const VerdictArgs& v, hipStream_t s);
+// A prompt's rows into the head-major cache: k, v [n][Hkv][row] -> [Hkv][pool_rows][row].
+hipError_t launch_prefill(const PrefillArgs& a, hipStream_t s);
 
 }  // namespace asrkf

@@ -2,15 +2,16 @@
 //
 // HBM layout of a context (cap = max_ctx + 1 rounded up to 64 positions;
 // pool_rows = cap in resident mode, the configured device rows in spill mode):
-//   K, V cache      [L][B][pool_rows][Hkv][D]   dtype   token-major rows
+//   K, V cache      [L][B][Hkv][pool_rows][D]   dtype   head-major rows
 //   unfreeze U      [L][B][cap]           int32   token attends at step t iff U <= t
 //   count c         [L][B][cap]           int32   low-relevance detections (Eq. 3)
 //   score flag      [L][B][cap]           uint8   s_j < tau at the current step (Eq. 2)
 //   active list     [L][B][cap]           int32   ascending positions for the step
 //   n_active        [L][B]                int32
-//   partials        [grid+B][Hq][D+2]     fp32    split-K attention partials
-//   plan records    [L][grid][36]         int32   first tile of every attention range
-//                                                 (resident mode, four or more layers)
+//   relevance       [L][B][planes][cap]   fp32    products of the attended tokens, by list
+//                                                 entry: planes = Hkv (Eq. 2) or Hq (softmax)
+//   partials        [grid+B*Hkv][heads][D+2] fp32 split-K attention partials
+//   tickets         [B][Hkv]              int32   arrivals at a shared pair, zero between launches
 //   per sequence    prompt length, escalation, level, entropy, p_max
 //   duration table  [max_ctx + 2]         int32   d(c) of Eq. 3, built exactly on the host
 // Spill mode adds, per (layer, sequence): the device row of every position,
@@ -97,7 +98,8 @@ struct asrkf_ctx {
     size_t esz = 0;
     size_t row_bytes = 0;        // one token, all KV heads
     int grid = 0;                // attention grid (resident workgroups)
-    int n_slots = 0;             // partial slots: grid + batch
+    int heads_per_group = 1;     // KV heads a workgroup takes together (set for each step)
+    int launch = 0;              // workgroups of the step's attention launches
     int dur_len = 0;
 
     // device memory
@@ -116,9 +118,9 @@ struct asrkf_ctx {
     float* pmax = nullptr;
     float* part_acc = nullptr;
     float* part_ml = nullptr;
-    int32_t* slot_info = nullptr;   // [2B]: first slot, end slot per sequence
-    int32_t* plan = nullptr;        // [state_layers][grid][kPlanInts] first-tile records of the
-                                    // attention ranges (resident mode, several layers), or null
+    int32_t* ticket = nullptr;      // [B][Hkv]
+    int planes = 0;                 // relevance planes: n_kv_heads, or n_q_heads (softmax reading)
+    float* rel = nullptr;           // [L][B][planes][cap]
     float* ent_partial = nullptr;   // [B][kEntropySplitMax][3]
     int32_t* ent_ticket = nullptr;  // [B]
     unsigned long long* counters = nullptr;   // [0] listed_total, [1..3] recoveries, [5] rr,
@@ -130,9 +132,7 @@ struct asrkf_ctx {
     int state_layers = 0;         // layers that own token states: n_layers, or 1
     uint64_t* hmask = nullptr;    // [state_layers][B][cap] (history window)
     int32_t* hlast = nullptr;
-    float* rel_acc = nullptr;     // [B][cap] (token scope)
-    float* xlog = nullptr;        // [B][cap][Hq] (relevance by attention weight)
-    float* norm = nullptr;        // [B][Hq][2]
+    float* norm = nullptr;        // [L][B][Hq][2] (relevance by attention weight)
     int n_seg = 1, seg_len = 0;   // segmented list rebuild (few, long instances)
     int32_t* seg_count = nullptr; // [state instances][n_seg]
 
@@ -229,11 +229,11 @@ asrkf_status dev_alloc(asrkf_ctx* ctx, T** p, size_t bytes) {
 void free_all(asrkf_ctx* ctx) {
     void* ptrs[] = {ctx->kpool, ctx->vpool, ctx->unfreeze, ctx->count, ctx->flag, ctx->list,
                     ctx->n_active, ctx->plen, ctx->dur, ctx->escalation, ctx->level,
-                    ctx->entropy, ctx->pmax, ctx->part_acc, ctx->part_ml, ctx->slot_info, ctx->ent_partial, ctx->ent_ticket,
+                    ctx->entropy, ctx->pmax, ctx->part_acc, ctx->part_ml, ctx->ticket, ctx->rel, ctx->ent_partial, ctx->ent_ticket,
                     ctx->counters, ctx->row_of, ctx->on_host, ctx->list_row, ctx->last_row,
                     ctx->row_owner, ctx->hand, ctx->pop_buf, ctx->out_pos, ctx->out_row, ctx->n_out, ctx->in_pos, ctx->in_row,
-                    ctx->n_in, ctx->flags, ctx->t_dev, ctx->hmask, ctx->hlast, ctx->rel_acc, ctx->xlog,
-                    ctx->norm, ctx->seg_count, ctx->plan};
+                    ctx->n_in, ctx->flags, ctx->t_dev, ctx->hmask, ctx->hlast,
+                    ctx->norm, ctx->seg_count};
     for (void* p : ptrs) if (p) (void)hipFree(p);
     void* host[] = {ctx->khost, ctx->vhost, ctx->flags_host};
     for (void* p : host) if (p) (void)hipHostFree(p);
@@ -315,6 +315,20 @@ hipError_t follow_last_stream(asrkf_ctx* ctx, hipStream_t s) {
     return e;
 }
 
+// Split partials, in query heads: one slot per workgroup and pair, each for the
+// heads of a piece (at most eight KV heads).
+size_t part_heads(const asrkf_ctx* ctx) {
+    const asrkf_config& c = ctx->cfg;
+    return (size_t)ctx->grid * std::min(c.n_kv_heads, 8) * ctx->group + (size_t)c.batch * c.n_q_heads;
+}
+
+// Bytes that asrkf_decode_step_static documents for its partials; what a
+// context needs is never more.
+size_t partial_bytes(const asrkf_ctx* ctx) {
+    const asrkf_config& c = ctx->cfg;
+    return ((size_t)ctx->grid + c.batch) * c.n_q_heads * (c.head_dim + 2) * 4 + (size_t)c.batch * 2 * 4;
+}
+
 void mark_queued(asrkf_ctx* ctx, hipStream_t s) {
     ctx->last_stream = s;
     ctx->queued = true;
@@ -380,7 +394,7 @@ asrkf_status asrkf_init(const asrkf_config* cfg, asrkf_ctx** out) {
         }
         ctx->grid = per_cu * prop.multiProcessorCount;
     }
-    ctx->n_slots = ctx->grid + c.batch;
+    ctx->planes = c.relevance == ASRKF_REL_SOFTMAX ? c.n_q_heads : c.n_kv_heads;
     ctx->dur_len = c.max_ctx + 2;
     ctx->spill = c.spill_min_D > 0;
     ctx->pool_rows = ctx->spill && c.device_rows > 0 ? c.device_rows : ctx->cap;
@@ -407,13 +421,10 @@ asrkf_status asrkf_init(const asrkf_config* cfg, asrkf_ctx** out) {
         ALLOC(hmask, st_pos * 8);
         ALLOC(hlast, st_pos * 4);
     }
-    if (ctx->token_scope) ALLOC(rel_acc, (size_t)c.batch * ctx->cap * 4);
+    ALLOC(rel, per_pos * ctx->planes * 4);
     ctx->n_seg = compact_segments((int)st_inst, ctx->cap, &ctx->seg_len);
     if (ctx->n_seg > 1) ALLOC(seg_count, st_inst * (ctx->n_seg + 1) * 32);   // spill mode: 8 counts per segment
-    if (c.relevance == ASRKF_REL_SOFTMAX) {
-        ALLOC(xlog, (size_t)c.batch * ctx->cap * c.n_q_heads * 4);
-        ALLOC(norm, (size_t)c.batch * c.n_q_heads * 2 * 4);
-    }
+    if (c.relevance == ASRKF_REL_SOFTMAX) ALLOC(norm, inst * c.n_q_heads * 2 * 4);
     ALLOC(n_active, inst * 4);
     ALLOC(plen, (size_t)c.batch * 4);
     ALLOC(dur, (size_t)ctx->dur_len * 4);
@@ -421,13 +432,9 @@ asrkf_status asrkf_init(const asrkf_config* cfg, asrkf_ctx** out) {
     ALLOC(level, (size_t)c.batch * 4);
     ALLOC(entropy, (size_t)c.batch * 4);
     ALLOC(pmax, (size_t)c.batch * 4);
-    ALLOC(part_acc, (size_t)ctx->n_slots * c.n_q_heads * c.head_dim * 4);
-    ALLOC(part_ml, (size_t)ctx->n_slots * c.n_q_heads * 2 * 4);
-    ALLOC(slot_info, (size_t)c.batch * 2 * 4);
-    // The first-tile records cost a launch per step and save about a memory round
-    // trip per attention launch: worth it from a few layers on.
-    if (!ctx->spill && c.n_layers >= kPlanMinLayers)
-        ALLOC(plan, (size_t)ctx->state_layers * ctx->grid * kPlanInts * 4);
+    ALLOC(part_acc, part_heads(ctx) * c.head_dim * 4);
+    ALLOC(part_ml, part_heads(ctx) * 2 * 4);
+    ALLOC(ticket, (size_t)c.batch * c.n_kv_heads * 4);
     ALLOC(ent_partial, (size_t)c.batch * kEntropySplitMax * 3 * 4);
     ALLOC(ent_ticket, (size_t)c.batch * 4);
     ALLOC(counters, kCounters * sizeof(unsigned long long));
@@ -497,6 +504,7 @@ asrkf_status asrkf_init(const asrkf_config* cfg, asrkf_ctx** out) {
     INIT(hipMemset(ctx->unfreeze, 0, st_pos * 4));
     INIT(hipMemset(ctx->count, 0, st_pos * 4));
     INIT(hipMemset(ctx->n_active, 0, st_inst * 4));
+    INIT(hipMemset(ctx->ticket, 0, (size_t)c.batch * c.n_kv_heads * 4));
     if (ctx->hmask) INIT(hipMemset(ctx->hmask, 0, st_pos * 8));
     if (ctx->hlast) INIT(hipMemset(ctx->hlast, 0, st_pos * 4));
     INIT(hipMemset(ctx->plen, 0, (size_t)c.batch * 4));
@@ -536,15 +544,20 @@ asrkf_status asrkf_prefill(asrkf_ctx* ctx, int32_t layer, int32_t seq, const voi
     hipStream_t s = static_cast<hipStream_t>(stream);
     HIP_OK(ctx, follow_last_stream(ctx, s));
     const size_t off = ((size_t)layer * c.batch + seq) * ctx->pool_rows * ctx->row_bytes;
-    const size_t bytes = (size_t)n_tokens * ctx->row_bytes;
-    HIP_OK(ctx, hipMemcpyAsync((char*)ctx->kpool + off, k, bytes, hipMemcpyDeviceToDevice, s));
-    HIP_OK(ctx, hipMemcpyAsync((char*)ctx->vpool + off, v, bytes, hipMemcpyDeviceToDevice, s));
-    if (!ctx->prefilled[seq]) {
-        ctx->prefilled[seq] = 1;
-        ctx->plen_host[seq] = n_tokens;
-        HIP_OK(ctx, hipMemcpyAsync(ctx->plen + seq, &ctx->plen_host[seq], 4,
-                                   hipMemcpyHostToDevice, s));
-    }
+    PrefillArgs p{};
+    p.k = static_cast<const char*>(k);
+    p.v = static_cast<const char*>(v);
+    p.kdst = static_cast<char*>(ctx->kpool) + off;
+    p.vdst = static_cast<char*>(ctx->vpool) + off;
+    p.plen = ctx->plen + seq;
+    p.n = n_tokens;
+    p.Hkv = c.n_kv_heads;
+    p.row_bytes = (int32_t)(c.head_dim * ctx->esz);
+    p.pool_rows = ctx->pool_rows;
+    p.set_plen = ctx->prefilled[seq] ? 0 : 1;
+    HIP_OK(ctx, launch_prefill(p, s));
+    ctx->prefilled[seq] = 1;
+    ctx->plen_host[seq] = n_tokens;
     mark_queued(ctx, s);
     return ASRKF_OK;
 }
@@ -589,10 +602,6 @@ asrkf_status build_lists(asrkf_ctx* ctx, int forced_level, hipStream_t s) {
     a.seg_count = ctx->seg_count;
     // the freeze loop of the step that ends here (the kernels skip it before step 1)
     a.flag = ctx->flag;
-    a.scope_token = ctx->token_scope ? 1 : 0;
-    a.rel_acc = ctx->rel_acc;
-    a.tau_LH = ctx->cfg.tau * (float)ctx->cfg.n_layers * (float)ctx->cfg.n_q_heads;
-    a.margin_LH = ctx->cfg.debug_margin * (float)ctx->cfg.n_layers * (float)ctx->cfg.n_q_heads;
     a.margin_hits = ctx->cfg.debug_margin > 0.f ? ctx->counters + 12 : nullptr;
     a.count = ctx->count;
     a.hmask = ctx->hmask;
@@ -621,19 +630,7 @@ asrkf_status build_lists(asrkf_ctx* ctx, int forced_level, hipStream_t s) {
         a.xfer = ctx->counters + 8;
     }
     HIP_OK(ctx, launch_compact(a, n_inst, s));
-    if (!ctx->spill) {
-        if (ctx->plan) {
-            PlanArgs p{};
-            p.list = ctx->list;
-            p.n_active = ctx->n_active;
-            p.plan = ctx->plan;
-            p.B = ctx->cfg.batch;
-            p.cap = ctx->cap;
-            p.grid = ctx->grid;
-            HIP_OK(ctx, launch_plan(p, ctx->state_layers, s));
-        }
-        return ASRKF_OK;
-    }
+    if (!ctx->spill) return ASRKF_OK;
 
     // the flag tells the host (one step late, without a wait) that rows ran out
     HIP_OK(ctx, hipMemcpyAsync(ctx->flags_host, ctx->flags, 8, hipMemcpyDeviceToHost, s));
@@ -654,6 +651,7 @@ asrkf_status build_lists(asrkf_ctx* ctx, int forced_level, hipStream_t s) {
     x.cap = ctx->cap;
     x.pool_rows = ctx->pool_rows;
     x.row_bytes = (int32_t)ctx->row_bytes;
+    x.Hkv = ctx->cfg.n_kv_heads;
     x.pos = ctx->out_pos;
     x.row = ctx->out_row;
     x.count = ctx->n_out;
@@ -707,12 +705,6 @@ asrkf_status check_overflow(asrkf_ctx* ctx, bool synced) {
 
 namespace {
 
-// Bytes of the split partials (acc, (m, l), slot range per sequence).
-size_t partial_bytes(const asrkf_ctx* ctx) {
-    const asrkf_config& c = ctx->cfg;
-    return (size_t)ctx->n_slots * c.n_q_heads * (c.head_dim + 2) * 4 + (size_t)c.batch * 2 * 4;
-}
-
 // decode_step with its split partials in the context's scratch, or (use_static)
 // in the static array, with no event of its own.
 asrkf_status decode_step_impl(asrkf_ctx* ctx, int32_t layer, const void* q, const void* k_new,
@@ -746,6 +738,11 @@ asrkf_status decode_step_impl(asrkf_ctx* ctx, int32_t layer, const void* q, cons
     if (st != ASRKF_OK) return st;
     HIP_OK(ctx, follow_last_stream(ctx, s));
     mark_queued(ctx, s);
+    if (layer == 0) {
+        attention_layout(ctx->plen_host.data(), c.batch, t, c.n_kv_heads, (int)(c.head_dim * ctx->esz), ctx->grid,
+                         &ctx->heads_per_group, &ctx->launch);
+        if (capture) ctx->launch = ctx->grid;    // replayed at later, longer steps
+    }
     if (!ctx->lists_ready) {
         if (ctx->spill)
             for (int b = 0; b < c.batch; ++b)
@@ -774,31 +771,25 @@ asrkf_status decode_step_impl(asrkf_ctx* ctx, int32_t layer, const void* q, cons
     a.pool_rows = ctx->pool_rows;
     a.spill = ctx->spill ? 1 : 0;
     a.n_active = ctx->n_active + st0;
-    a.flag = ctx->flag + st0 * ctx->cap;
     a.t_dev = layer == 0 ? ctx->t_dev : nullptr;
     a.rel_mode = c.relevance;
-    a.scope_token = ctx->token_scope ? 1 : 0;
-    a.first_layer = layer == 0 ? 1 : 0;
-    a.rel_acc = ctx->rel_acc;
-    a.xlog = ctx->xlog;
+    a.rel = ctx->rel + inst0 * ctx->planes * ctx->cap;
     a.part_acc = ctx->part_acc;
     a.part_ml = ctx->part_ml;
-    a.slot_first = ctx->slot_info;
-    a.slot_end = ctx->slot_info + c.batch;
-    a.plan = ctx->plan ? ctx->plan + (ctx->token_scope ? 0 : (size_t)layer) * ctx->grid * kPlanInts : nullptr;
+    a.ticket = ctx->ticket;
+    a.out = out;
+    a.norm = ctx->norm ? ctx->norm + inst0 * c.n_q_heads * 2 : nullptr;
+    a.planes = ctx->planes;
+    a.grid = ctx->grid;
+    a.heads_per_group = ctx->heads_per_group;
     if (use_static) {
-        float* base = static_cast<float*>(ctx->static_scratch);
-        a.part_acc = base;
-        a.part_ml = base + (size_t)ctx->n_slots * c.n_q_heads * c.head_dim;
-        a.slot_first = reinterpret_cast<int32_t*>(a.part_ml + (size_t)ctx->n_slots * c.n_q_heads * 2);
-        a.slot_end = a.slot_first + c.batch;
+        a.part_acc = static_cast<float*>(ctx->static_scratch);
+        a.part_ml = a.part_acc + part_heads(ctx) * c.head_dim;
     }
     a.B = c.batch;
     a.cap = ctx->cap;
     a.Hq = c.n_q_heads;
     a.Hkv = c.n_kv_heads;
-    a.tau_H = c.tau * (float)c.n_q_heads;
-    a.margin_H = c.debug_margin * (float)c.n_q_heads;
     a.scale_log2 = (float)(1.4426950408889634 / sqrt((double)c.head_dim));
 
     std::pair<hipEvent_t, hipEvent_t> ev{nullptr, nullptr};
@@ -813,37 +804,9 @@ asrkf_status decode_step_impl(asrkf_ctx* ctx, int32_t layer, const void* q, cons
             HIP_OK(ctx, hipEventCreateWithFlags(&ev.second, hipEventDisableSystemFence));
         }
     }
-    HIP_OK(ctx, launch_attention(a, c.dtype == ASRKF_BF16, c.head_dim, ctx->group, ctx->grid, s,
+    HIP_OK(ctx, launch_attention(a, c.dtype == ASRKF_BF16, c.head_dim, ctx->group, ctx->launch, s,
                                  ev.first, ev.second));
     if (ev.first) ctx->ev_used.push_back(ev);
-
-    FinishArgs f{};
-    f.part_acc = a.part_acc;
-    f.part_ml = a.part_ml;
-    f.slot_first = a.slot_first;
-    f.slot_end = a.slot_end;
-    f.out = out;
-    f.norm = ctx->norm;
-    f.B = c.batch;
-    f.Hq = c.n_q_heads;
-    HIP_OK(ctx, launch_finish(f, c.head_dim, ctx->grid / c.batch + 1, s));
-    if (c.relevance == ASRKF_REL_SOFTMAX) {
-        RelevanceArgs r{};
-        r.xlog = ctx->xlog;
-        r.norm = ctx->norm;
-        r.list = a.list;
-        r.n_active = a.n_active;
-        r.flag = a.flag;
-        r.rel_acc = ctx->rel_acc;
-        r.B = c.batch;
-        r.cap = ctx->cap;
-        r.Hq = c.n_q_heads;
-        r.scope_token = a.scope_token;
-        r.first_layer = a.first_layer;
-        r.tau_H = a.tau_H;
-        r.margin_H = a.margin_H;
-        HIP_OK(ctx, launch_weight_relevance(r, s));
-    }
 
     ctx->next_layer = layer + 1;
     return ASRKF_OK;
@@ -882,8 +845,8 @@ asrkf_status asrkf_restore(asrkf_ctx* ctx, const float* logits, int32_t mode, vo
     HIP_OK(ctx, follow_last_stream(ctx, s));
     mark_queued(ctx, s);
     int forced;
+    EntropyArgs e{};
     if (logits) {
-        EntropyArgs e{};
         e.logits = logits;
         e.partial = ctx->ent_partial;
         e.split = entropy_split(c.batch);
@@ -899,11 +862,26 @@ asrkf_status asrkf_restore(asrkf_ctx* ctx, const float* logits, int32_t mode, vo
         e.pmax = ctx->pmax;
         e.recoveries = ctx->counters;       // [level] for level 1..3
         e.rr_requests = ctx->counters + 5;
-        HIP_OK(ctx, launch_entropy(e, s));
         forced = -1;                           // level[] written by the entropy kernel
     } else {
         forced = (mode >= ASRKF_SR && mode <= ASRKF_FR) ? (int)mode : 0;
     }
+    VerdictArgs v{};
+    v.rel = ctx->rel;
+    v.norm = ctx->norm;
+    v.list = ctx->list;
+    v.n_active = ctx->n_active;
+    v.flag = ctx->flag;
+    v.B = c.batch;
+    v.cap = ctx->cap;
+    v.planes = ctx->planes;
+    v.used = c.relevance == ASRKF_REL_SOFTMAX ? c.n_q_heads : c.n_kv_heads / ctx->heads_per_group;
+    v.softmax = c.relevance == ASRKF_REL_SOFTMAX ? 1 : 0;
+    v.states = ctx->state_layers;
+    v.layers_summed = ctx->token_scope ? c.n_layers : 1;
+    v.tau_sum = c.tau * (float)v.layers_summed * (float)c.n_q_heads;
+    v.margin_sum = c.debug_margin * (float)v.layers_summed * (float)c.n_q_heads;
+    HIP_OK(ctx, launch_monitor(logits ? &e : nullptr, v, s));
     // a captured step runs only when replayed: the host learns of it from the
     // device step counter at its next wait
     if (!capturing(s)) ctx->t += 1;
