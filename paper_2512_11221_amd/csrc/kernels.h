@@ -97,14 +97,28 @@ struct VerdictArgs {
     float margin_sum;         // debug margin * Hq (* L); 0: off
 };
 
+// Entropy monitor of a sequence after the last restore (Sec. 3.6).
+struct SeqMonitor {
+    float entropy, pmax;
+    int32_t escalation, level;
+};
+
+// Arrays to zero (16-byte aligned, sizes in 32-bit words).
+constexpr int kMaxClear = 8;
+struct ClearArgs {
+    void* p[kMaxClear];
+    size_t words[kMaxClear];
+    int32_t n;
+};
+
 struct CompactArgs {
     int32_t* unfreeze;        // [L][B][cap]
     int32_t* list;            // [L][B][cap]
     int32_t* n_active;        // [L][B]
     const int32_t* plen;      // [B]
-    const int32_t* level;     // [B] recovery level per sequence (may be null)
+    const SeqMonitor* monitor;  // [B] recovery level per sequence (may be null)
     unsigned long long* listed_total;  // running sum of list lengths
-    int32_t forced_level;     // -1: read level[]; 0: none; 1..3 forced SR/WR/FR
+    int32_t forced_level;     // -1: read monitor[]; 0: none; 1..3 forced SR/WR/FR
     int32_t count_forced;     // 1: count a forced level (no logits) in recoveries[]
     unsigned long long* recoveries;  // [4], indexed by level 1..3
     const int32_t* t_dev;     // steps started (advanced by each step's first attention launch)
@@ -112,6 +126,7 @@ struct CompactArgs {
     int32_t max_ctx;          // positions per sequence; a rebuild that would pass it is refused
     int32_t* flags;           // [0] a sequence ran out of device rows (spill mode),
                               // [1] a step would pass max_ctx positions
+    int32_t* flag_host;       // spill mode: flags[0] in pinned host memory
     int32_t B, cap, wr_last_N;
     // spill mode only (spill_min_D > 0)
     int32_t spill_min_D;
@@ -202,10 +217,7 @@ struct EntropyArgs {
     int32_t V, B;
     float theta_H, theta_p;
     int32_t mode;             // 0 AUTO, 1..3 forced, 4 none
-    int32_t* escalation;      // [B]
-    int32_t* level;           // [B] (written)
-    float* entropy;           // [B]
-    float* pmax;              // [B]
+    SeqMonitor* monitor;      // [B] (updated)
     unsigned long long* recoveries;  // [4], indexed by level 1..3
     unsigned long long* rr_requests;
 };
@@ -220,9 +232,10 @@ hipError_t attention_occupancy(const AttnArgs& a, int dtype_bf16, int head_dim, 
 // launch (at least those with work, at most grid: idle ones delay the others).
 void attention_layout(const int32_t* plen, int batch, int t, int n_kv_heads, int row_bytes, int grid,
                       int* heads_per_group, int* launch);
+hipError_t launch_clear(const ClearArgs& a, hipStream_t s);
 hipError_t launch_compact(const CompactArgs& a, int n_instances, hipStream_t s);
 // Segments per instance (and their length) for the rebuild; 1 = one workgroup per instance.
-int compact_segments(int n_instances, int cap, int* seg_len);
+int compact_segments(int n_instances, int cap, bool spill, int* seg_len);
 hipError_t launch_spill_init(const SpillInitArgs& a, int n_instances, hipStream_t s);
 hipError_t launch_xfer(const XferArgs& a, int n_instances, hipStream_t s);
 // Whether the attention kernel handles this (dtype, head_dim, q heads per KV head, KV heads).

@@ -42,6 +42,14 @@ thread_local std::string g_last_error;
 
 constexpr int kCounters = 16;   // device counters of a context (see asrkf_ctx::counters)
 
+// What the waiting calls read back, one block on the device.
+struct Status {
+    unsigned long long counters[kCounters];
+    int32_t flags[2];
+    int32_t t;                  // steps started
+    int32_t pad;
+};
+
 asrkf_status fail(asrkf_status st, const char* fmt, ...) {
     char buf[512];
     va_list ap;
@@ -112,15 +120,16 @@ struct asrkf_ctx {
     int32_t* n_active = nullptr;
     int32_t* plen = nullptr;
     int32_t* dur = nullptr;
-    int32_t* escalation = nullptr;
-    int32_t* level = nullptr;
-    float* entropy = nullptr;
-    float* pmax = nullptr;
+    SeqMonitor* monitor = nullptr;  // [B]
     float* part_acc = nullptr;
     float* part_ml = nullptr;
     int32_t* ticket = nullptr;      // [B][Hkv]
     int planes = 0;                 // relevance planes: n_kv_heads, or n_q_heads (softmax reading)
     float* rel = nullptr;           // [L][B][planes][cap]
+    void* small = nullptr;          // one allocation for every small array: those cleared by a reset
+    size_t small_cleared = 0;       // come first, in so many bytes
+    Status* status = nullptr;       // counters, flags and t_dev below
+    Status* status_host = nullptr;  // pinned copy
     float* ent_partial = nullptr;   // [B][kEntropySplitMax][3]
     int32_t* ent_ticket = nullptr;  // [B]
     unsigned long long* counters = nullptr;   // [0] listed_total, [1..3] recoveries, [5] rr,
@@ -158,13 +167,12 @@ struct asrkf_ctx {
     void* vhost = nullptr;
     void* khost_dev = nullptr;    // the same memory as seen by kernels
     void* vhost_dev = nullptr;
-    int32_t* flags_host = nullptr;      // pinned copy of flags (spill mode, read without a wait)
+    int32_t* flags_host = nullptr;      // spill mode: out of rows, written by the kernels (pinned,
+    int32_t* flags_host_dev = nullptr;  // read without a wait), and as the kernels see it
     hipStream_t side = nullptr;   // copies to and from the host store
     hipEvent_t ev_lists = nullptr;      // compaction done (main stream)
-    hipEvent_t ev_flag = nullptr;       // flags copied to the host
     std::vector<hipEvent_t> ev_in;      // per layer: its restores are in the device cache
     bool xfer_recorded = false;
-    bool flag_recorded = false;
 
     std::vector<int32_t> plen_host;
     std::vector<char> prefilled;   // per sequence
@@ -227,19 +235,15 @@ asrkf_status dev_alloc(asrkf_ctx* ctx, T** p, size_t bytes) {
 }
 
 void free_all(asrkf_ctx* ctx) {
-    void* ptrs[] = {ctx->kpool, ctx->vpool, ctx->unfreeze, ctx->count, ctx->flag, ctx->list,
-                    ctx->n_active, ctx->plen, ctx->dur, ctx->escalation, ctx->level,
-                    ctx->entropy, ctx->pmax, ctx->part_acc, ctx->part_ml, ctx->ticket, ctx->rel, ctx->ent_partial, ctx->ent_ticket,
-                    ctx->counters, ctx->row_of, ctx->on_host, ctx->list_row, ctx->last_row,
-                    ctx->row_owner, ctx->hand, ctx->pop_buf, ctx->out_pos, ctx->out_row, ctx->n_out, ctx->in_pos, ctx->in_row,
-                    ctx->n_in, ctx->flags, ctx->t_dev, ctx->hmask, ctx->hlast,
-                    ctx->norm, ctx->seg_count};
+    void* ptrs[] = {ctx->kpool, ctx->vpool, ctx->unfreeze, ctx->count, ctx->flag, ctx->list, ctx->small,
+                    ctx->part_acc, ctx->rel, ctx->row_of, ctx->on_host, ctx->list_row, ctx->last_row,
+                    ctx->row_owner, ctx->pop_buf, ctx->out_pos, ctx->out_row, ctx->in_pos, ctx->in_row,
+                    ctx->hmask, ctx->hlast, ctx->seg_count};
     for (void* p : ptrs) if (p) (void)hipFree(p);
-    void* host[] = {ctx->khost, ctx->vhost, ctx->flags_host};
+    void* host[] = {ctx->khost, ctx->vhost, ctx->flags_host, ctx->status_host};
     for (void* p : host) if (p) (void)hipHostFree(p);
     if (ctx->side) (void)hipStreamDestroy(ctx->side);
     if (ctx->ev_lists) (void)hipEventDestroy(ctx->ev_lists);
-    if (ctx->ev_flag) (void)hipEventDestroy(ctx->ev_flag);
     if (ctx->ev_switch) (void)hipEventDestroy(ctx->ev_switch);
     for (hipEvent_t e : ctx->ev_in) if (e) (void)hipEventDestroy(e);
     for (auto& ev : ctx->ev_used) { (void)hipEventDestroy(ev.first); (void)hipEventDestroy(ev.second); }
@@ -327,6 +331,24 @@ size_t part_heads(const asrkf_ctx* ctx) {
 size_t partial_bytes(const asrkf_ctx* ctx) {
     const asrkf_config& c = ctx->cfg;
     return ((size_t)ctx->grid + c.batch) * c.n_q_heads * (c.head_dim + 2) * 4 + (size_t)c.batch * 2 * 4;
+}
+
+// The device state of a context that has run no step (every other array is
+// written before it is read).
+hipError_t clear_state(asrkf_ctx* ctx, hipStream_t s) {
+    const size_t st_pos = (size_t)ctx->state_layers * ctx->cfg.batch * ctx->cap;
+    ClearArgs a{};
+    auto add = [&](void* p, size_t bytes) {
+        if (!p) return;
+        a.p[a.n] = p;
+        a.words[a.n++] = bytes / 4;
+    };
+    add(ctx->small, ctx->small_cleared);
+    add(ctx->unfreeze, st_pos * 4);
+    add(ctx->count, st_pos * 4);
+    add(ctx->hmask, st_pos * 8);
+    add(ctx->hlast, st_pos * 4);
+    return launch_clear(a, s);
 }
 
 void mark_queued(asrkf_ctx* ctx, hipStream_t s) {
@@ -422,38 +444,52 @@ asrkf_status asrkf_init(const asrkf_config* cfg, asrkf_ctx** out) {
         ALLOC(hlast, st_pos * 4);
     }
     ALLOC(rel, per_pos * ctx->planes * 4);
-    ctx->n_seg = compact_segments((int)st_inst, ctx->cap, &ctx->seg_len);
+    ctx->n_seg = compact_segments((int)st_inst, ctx->cap, ctx->spill, &ctx->seg_len);
     if (ctx->n_seg > 1) ALLOC(seg_count, st_inst * (ctx->n_seg + 1) * 32);   // spill mode: 8 counts per segment
-    if (c.relevance == ASRKF_REL_SOFTMAX) ALLOC(norm, inst * c.n_q_heads * 2 * 4);
-    ALLOC(n_active, inst * 4);
-    ALLOC(plen, (size_t)c.batch * 4);
-    ALLOC(dur, (size_t)ctx->dur_len * 4);
-    ALLOC(escalation, (size_t)c.batch * 4);
-    ALLOC(level, (size_t)c.batch * 4);
-    ALLOC(entropy, (size_t)c.batch * 4);
-    ALLOC(pmax, (size_t)c.batch * 4);
     ALLOC(part_acc, part_heads(ctx) * c.head_dim * 4);
-    ALLOC(part_ml, part_heads(ctx) * 2 * 4);
-    ALLOC(ticket, (size_t)c.batch * c.n_kv_heads * 4);
-    ALLOC(ent_partial, (size_t)c.batch * kEntropySplitMax * 3 * 4);
-    ALLOC(ent_ticket, (size_t)c.batch * 4);
-    ALLOC(counters, kCounters * sizeof(unsigned long long));
-    ALLOC(flags, 8);
-    ALLOC(t_dev, 4);
+    {
+        // the small arrays, 256-byte aligned in one allocation
+        struct Small { void** p; size_t bytes; };
+        const size_t B = (size_t)c.batch;
+        const Small small[] = {
+            {(void**)&ctx->status, sizeof(Status)},            // cleared by a reset:
+            {(void**)&ctx->n_active, inst * 4},
+            {(void**)&ctx->plen, B * 4},
+            {(void**)&ctx->monitor, B * sizeof(SeqMonitor)},
+            {(void**)&ctx->ent_ticket, B * 4},
+            {(void**)&ctx->ticket, B * c.n_kv_heads * 4},
+            {(void**)&ctx->part_ml, part_heads(ctx) * 2 * 4},  // not cleared:
+            {(void**)&ctx->dur, (size_t)ctx->dur_len * 4},
+            {(void**)&ctx->ent_partial, B * kEntropySplitMax * 3 * 4},
+            {(void**)&ctx->norm, c.relevance == ASRKF_REL_SOFTMAX ? inst * c.n_q_heads * 2 * 4 : 0},
+            {(void**)&ctx->hand, ctx->spill ? inst * 4 : 0},
+            {(void**)&ctx->n_out, ctx->spill ? inst * 4 : 0},
+            {(void**)&ctx->n_in, ctx->spill ? inst * 4 : 0},
+        };
+        size_t total = 0;
+        for (const Small& x : small) total += (x.bytes + 255) / 256 * 256;
+        ALLOC(small, total);
+        char* at = static_cast<char*>(ctx->small);
+        for (const Small& x : small) {
+            if (x.p == (void**)&ctx->part_ml) ctx->small_cleared = at - static_cast<char*>(ctx->small);
+            *x.p = x.bytes ? at : nullptr;
+            at += (x.bytes + 255) / 256 * 256;
+        }
+        ctx->counters = ctx->status->counters;
+        ctx->flags = ctx->status->flags;
+        ctx->t_dev = &ctx->status->t;
+    }
     if (ctx->spill) {
         ALLOC(row_of, per_pos * 4);
         ALLOC(on_host, per_pos);
         ALLOC(list_row, per_pos * 4);
         ALLOC(last_row, per_pos * 4);
         ALLOC(row_owner, inst * ctx->pool_rows * 4);
-        ALLOC(hand, inst * 4);
         ALLOC(pop_buf, inst * ctx->pool_rows * 4);
         ALLOC(out_pos, per_pos * 4);
         ALLOC(out_row, per_pos * 4);
-        ALLOC(n_out, inst * 4);
         ALLOC(in_pos, per_pos * 4);
         ALLOC(in_row, per_pos * 4);
-        ALLOC(n_in, inst * 4);
         // host store: pinned, mapped, coarse-grained (only the GPU reads and writes it)
         const size_t store = per_pos * ctx->row_bytes;
         const unsigned flags = hipHostMallocMapped | hipHostMallocNonCoherent;
@@ -471,7 +507,7 @@ asrkf_status asrkf_init(const asrkf_config* cfg, asrkf_ctx** out) {
         if (he == hipSuccess) he = hipHostGetDevicePointer(&ctx->vhost_dev, ctx->vhost, 0);
         if (he == hipSuccess) he = hipStreamCreateWithFlags(&ctx->side, hipStreamNonBlocking);
         if (he == hipSuccess) he = hipEventCreateWithFlags(&ctx->ev_lists, hipEventDisableTiming);
-        if (he == hipSuccess) he = hipEventCreateWithFlags(&ctx->ev_flag, hipEventDisableTiming);
+        if (he == hipSuccess) he = hipHostGetDevicePointer((void**)&ctx->flags_host_dev, ctx->flags_host, 0);
         ctx->ev_in.assign(c.n_layers, nullptr);
         for (int l = 0; l < c.n_layers && he == hipSuccess; ++l)
             he = hipEventCreateWithFlags(&ctx->ev_in[l], hipEventDisableTiming);
@@ -485,7 +521,8 @@ asrkf_status asrkf_init(const asrkf_config* cfg, asrkf_ctx** out) {
 #undef ALLOC
 
     {
-        const hipError_t he = hipEventCreateWithFlags(&ctx->ev_switch, hipEventDisableTiming);
+        hipError_t he = hipEventCreateWithFlags(&ctx->ev_switch, hipEventDisableTiming);
+        if (he == hipSuccess) he = hipHostMalloc((void**)&ctx->status_host, sizeof(Status), hipHostMallocDefault);
         if (he != hipSuccess) {
             st = hip_fail(nullptr, he, "hipEventCreateWithFlags");
             free_all(ctx);
@@ -501,21 +538,7 @@ asrkf_status asrkf_init(const asrkf_config* cfg, asrkf_ctx** out) {
         hipError_t e_ = (expr);                                                 \
         if (e_ != hipSuccess) { st = hip_fail(nullptr, e_, #expr); free_all(ctx); delete ctx; return st; } \
     } while (0)
-    INIT(hipMemset(ctx->unfreeze, 0, st_pos * 4));
-    INIT(hipMemset(ctx->count, 0, st_pos * 4));
-    INIT(hipMemset(ctx->n_active, 0, st_inst * 4));
-    INIT(hipMemset(ctx->ticket, 0, (size_t)c.batch * c.n_kv_heads * 4));
-    if (ctx->hmask) INIT(hipMemset(ctx->hmask, 0, st_pos * 8));
-    if (ctx->hlast) INIT(hipMemset(ctx->hlast, 0, st_pos * 4));
-    INIT(hipMemset(ctx->plen, 0, (size_t)c.batch * 4));
-    INIT(hipMemset(ctx->escalation, 0, (size_t)c.batch * 4));
-    INIT(hipMemset(ctx->level, 0, (size_t)c.batch * 4));
-    INIT(hipMemset(ctx->entropy, 0, (size_t)c.batch * 4));
-    INIT(hipMemset(ctx->pmax, 0, (size_t)c.batch * 4));
-    INIT(hipMemset(ctx->ent_ticket, 0, (size_t)c.batch * 4));
-    INIT(hipMemset(ctx->counters, 0, kCounters * sizeof(unsigned long long)));
-    INIT(hipMemset(ctx->flags, 0, 8));
-    INIT(hipMemset(ctx->t_dev, 0, 4));
+    INIT(clear_state(ctx, nullptr));
     INIT(hipMemcpy(ctx->dur, table.data(), table.size() * 4, hipMemcpyHostToDevice));
     INIT(hipDeviceSynchronize());
 #undef INIT
@@ -586,7 +609,7 @@ asrkf_status build_lists(asrkf_ctx* ctx, int forced_level, hipStream_t s) {
     a.list = ctx->list;
     a.n_active = ctx->n_active;
     a.plen = ctx->plen;
-    a.level = ctx->level;
+    a.monitor = ctx->monitor;
     a.listed_total = ctx->counters;
     a.forced_level = forced_level;
     a.count_forced = forced_level > 0 ? 1 : 0;       // no logits: the entropy kernel counts none
@@ -628,14 +651,10 @@ asrkf_status build_lists(asrkf_ctx* ctx, int forced_level, hipStream_t s) {
         a.in_row = ctx->in_row;
         a.n_in = ctx->n_in;
         a.xfer = ctx->counters + 8;
+        a.flag_host = ctx->flags_host_dev;
     }
     HIP_OK(ctx, launch_compact(a, n_inst, s));
     if (!ctx->spill) return ASRKF_OK;
-
-    // the flag tells the host (one step late, without a wait) that rows ran out
-    HIP_OK(ctx, hipMemcpyAsync(ctx->flags_host, ctx->flags, 8, hipMemcpyDeviceToHost, s));
-    HIP_OK(ctx, hipEventRecord(ctx->ev_flag, s));
-    ctx->flag_recorded = true;
 
     // copies on the side stream: every out-list first (its rows may be handed
     // out again below), then each layer's in-list, which that layer's next
@@ -679,14 +698,11 @@ asrkf_status build_lists(asrkf_ctx* ctx, int forced_level, hipStream_t s) {
 asrkf_status check_overflow(asrkf_ctx* ctx, bool synced) {
     int32_t f[2] = {0, 0};
     if (synced) {
-        HIP_OK(ctx, hipMemcpy(f, ctx->flags, 8, hipMemcpyDeviceToHost));
+        f[0] = ctx->status_host->flags[0];
+        f[1] = ctx->status_host->flags[1];
     } else {
-        if (!ctx->spill || !ctx->flag_recorded) return ASRKF_OK;
-        const hipError_t q = hipEventQuery(ctx->ev_flag);
-        if (q == hipErrorNotReady) return ASRKF_OK;
-        if (q != hipSuccess) return hip_fail(ctx, q, "hipEventQuery");
+        if (!ctx->spill) return ASRKF_OK;
         f[0] = ((volatile int32_t*)ctx->flags_host)[0];
-        f[1] = ((volatile int32_t*)ctx->flags_host)[1];
     }
     if (f[0]) {
         ctx->poisoned = true;
@@ -856,10 +872,7 @@ asrkf_status asrkf_restore(asrkf_ctx* ctx, const float* logits, int32_t mode, vo
         e.theta_H = c.entropy_spike;
         e.theta_p = c.conf_drop;
         e.mode = (int)mode;
-        e.escalation = ctx->escalation;
-        e.level = ctx->level;
-        e.entropy = ctx->entropy;
-        e.pmax = ctx->pmax;
+        e.monitor = ctx->monitor;
         e.recoveries = ctx->counters;       // [level] for level 1..3
         e.rr_requests = ctx->counters + 5;
         forced = -1;                           // level[] written by the entropy kernel
@@ -900,11 +913,11 @@ namespace {
 // counter: after the wait the host adopts it (the counter counts steps
 // started, so a step in progress is not yet complete).
 asrkf_status sync_ctx(asrkf_ctx* ctx) {
+    // the status block comes back behind the queued work: one wait for both
+    HIP_OK(ctx, hipMemcpyAsync(ctx->status_host, ctx->status, sizeof(Status), hipMemcpyDeviceToHost, ctx->last_stream));
     HIP_OK(ctx, hipStreamSynchronize(ctx->last_stream));
     if (ctx->side) HIP_OK(ctx, hipStreamSynchronize(ctx->side));
-    int32_t started = 0;
-    HIP_OK(ctx, hipMemcpy(&started, ctx->t_dev, 4, hipMemcpyDeviceToHost));
-    const int completed = started - (ctx->next_layer != 0 ? 1 : 0);
+    const int completed = ctx->status_host->t - (ctx->next_layer != 0 ? 1 : 0);
     if (completed > ctx->t) ctx->t = completed;
     return ASRKF_OK;
 }
@@ -940,9 +953,8 @@ asrkf_status asrkf_stats(asrkf_ctx* ctx, asrkf_stats_t* out) {
     const size_t inst = (size_t)ctx->state_layers * c.batch;
     // with token scope one list serves every layer: count it once per layer
     const int64_t per_list = ctx->token_scope ? c.n_layers : 1;
-    unsigned long long cnt[kCounters];
+    const unsigned long long* cnt = ctx->status_host->counters;
     std::vector<int32_t> na(inst);
-    HIP_OK(ctx, hipMemcpy(cnt, ctx->counters, sizeof cnt, hipMemcpyDeviceToHost));
     HIP_OK(ctx, hipMemcpy(na.data(), ctx->n_active, inst * 4, hipMemcpyDeviceToHost));
     memset(out, 0, sizeof *out);
     out->step = ctx->t;
@@ -1095,10 +1107,12 @@ asrkf_status asrkf_get_seq(asrkf_ctx* ctx, int32_t seq, float* entropy, float* p
     if (seq < 0 || seq >= ctx->cfg.batch) return fail(ASRKF_EINVAL, "sequence out of range");
     st = sync_ctx(ctx);
     if (st != ASRKF_OK) return st;
-    if (entropy) HIP_OK(ctx, hipMemcpy(entropy, ctx->entropy + seq, 4, hipMemcpyDeviceToHost));
-    if (pmax) HIP_OK(ctx, hipMemcpy(pmax, ctx->pmax + seq, 4, hipMemcpyDeviceToHost));
-    if (escalation) HIP_OK(ctx, hipMemcpy(escalation, ctx->escalation + seq, 4, hipMemcpyDeviceToHost));
-    if (level) HIP_OK(ctx, hipMemcpy(level, ctx->level + seq, 4, hipMemcpyDeviceToHost));
+    SeqMonitor m{};
+    HIP_OK(ctx, hipMemcpy(&m, ctx->monitor + seq, sizeof m, hipMemcpyDeviceToHost));
+    if (entropy) *entropy = m.entropy;
+    if (pmax) *pmax = m.pmax;
+    if (escalation) *escalation = m.escalation;
+    if (level) *level = m.level;
     return ASRKF_OK;
 }
 
@@ -1112,26 +1126,9 @@ asrkf_status asrkf_reset(asrkf_ctx* ctx) {
     st = collect_timing(ctx);
     if (st != ASRKF_OK) return st;
     const asrkf_config& c = ctx->cfg;
-    const size_t st_inst = (size_t)ctx->state_layers * c.batch;
-    const size_t st_pos = st_inst * ctx->cap;
-    // the device state of a context that has run no step: the same values asrkf_init
-    // writes (every other array is written before it is read again), on the stream
-    // of the context's last work, which has just drained
+    // on the stream of the context's last work, which has just drained
     hipStream_t s = ctx->last_stream;
-    HIP_OK(ctx, hipMemsetAsync(ctx->unfreeze, 0, st_pos * 4, s));
-    HIP_OK(ctx, hipMemsetAsync(ctx->count, 0, st_pos * 4, s));
-    HIP_OK(ctx, hipMemsetAsync(ctx->n_active, 0, st_inst * 4, s));
-    if (ctx->hmask) HIP_OK(ctx, hipMemsetAsync(ctx->hmask, 0, st_pos * 8, s));
-    if (ctx->hlast) HIP_OK(ctx, hipMemsetAsync(ctx->hlast, 0, st_pos * 4, s));
-    HIP_OK(ctx, hipMemsetAsync(ctx->plen, 0, (size_t)c.batch * 4, s));
-    HIP_OK(ctx, hipMemsetAsync(ctx->escalation, 0, (size_t)c.batch * 4, s));
-    HIP_OK(ctx, hipMemsetAsync(ctx->level, 0, (size_t)c.batch * 4, s));
-    HIP_OK(ctx, hipMemsetAsync(ctx->entropy, 0, (size_t)c.batch * 4, s));
-    HIP_OK(ctx, hipMemsetAsync(ctx->pmax, 0, (size_t)c.batch * 4, s));
-    HIP_OK(ctx, hipMemsetAsync(ctx->ent_ticket, 0, (size_t)c.batch * 4, s));
-    HIP_OK(ctx, hipMemsetAsync(ctx->counters, 0, kCounters * sizeof(unsigned long long), s));
-    HIP_OK(ctx, hipMemsetAsync(ctx->flags, 0, 8, s));
-    HIP_OK(ctx, hipMemsetAsync(ctx->t_dev, 0, 4, s));
+    HIP_OK(ctx, clear_state(ctx, s));
     HIP_OK(ctx, hipStreamSynchronize(s));
     if (ctx->flags_host) ctx->flags_host[0] = ctx->flags_host[1] = 0;
     ctx->plen_host.assign(c.batch, 0);
@@ -1140,7 +1137,6 @@ asrkf_status asrkf_reset(asrkf_ctx* ctx) {
     ctx->next_layer = 0;
     ctx->lists_ready = false;
     ctx->xfer_recorded = false;
-    ctx->flag_recorded = false;
     ctx->timing = false;
     ctx->attn_ms_done = 0.0;
     ctx->attn_launches = 0;
