@@ -79,7 +79,7 @@ prefill_kernel(PrefillArgs a) {
             if (i < total) {
                 const unsigned e = i & (per_row - 1), row = i >> row_shift;
                 const unsigned g = row & (a.Hkv - 1), p = row >> head_shift;
-                dst[((size_t)g * a.pool_rows + p) * per_row + e] = x[u];
+                __builtin_nontemporal_store(x[u], dst + ((size_t)g * a.pool_rows + p) * per_row + e);
             }
         }
     }
