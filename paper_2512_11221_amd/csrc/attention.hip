@@ -1042,18 +1042,21 @@ void attention_layout(const int32_t* plen, int batch, int t, int n_kv_heads, int
     const int tile = 8192 / row_bytes;
     int64_t tiles = 0;
     for (int b = 0; b < batch; ++b) tiles += (plen[b] + tile) / tile;
-    // One KV head per piece while the pieces are short: a pair's partials and its
-    // merge are smallest, and its relevance values are stored once, at the end.  With
-    // many pairs a workgroup would walk several short pieces one after the other,
-    // each with its own round trips, and with long pieces the relevance values of
-    // every KV head would be stored among the row loads, where they cost ten times
-    // their bytes (64 x 17k tokens: 730 us a launch with one head, 670 with eight,
-    // whose values are summed first): then the waves take heads side by side.  The
-    // choice rests on the prompts alone, so a step replayed from a graph is dealt
-    // like the same step run eagerly.
+    // One KV head per piece while every pair can have a workgroup and the pieces are
+    // short: a pair's partials and its merge are smallest, and its relevance values
+    // are stored once, at the end.  With more pairs a workgroup would walk several
+    // short pieces one after the other, each with its own round trips: the waves take
+    // as many heads side by side as bring the pairs down to the workgroups, and no
+    // more (16 x 100 to 900 tokens, 32 heads: 33.1 us a launch with one head, 29.0
+    // with two; 128 x 100 to 500 tokens, 8 heads: 49.0 us with eight, 42.3 with four).
+    // With long pieces the relevance values of every head would be stored among the
+    // row loads, where they cost ten times their bytes: eight heads, whose values are
+    // summed first (64 x 17k tokens: 730 us with one head, 670 with eight).  The
+    // choice rests on the prompts alone, so a step replayed from a graph is dealt like
+    // the same step run eagerly.
     int hw = 1;
-    if (tiles * n_kv_heads > (int64_t)room_tiles(tile) * grid || (int64_t)batch * n_kv_heads > 2 * (int64_t)grid)
-        hw = n_kv_heads < 8 ? n_kv_heads : 8;
+    if (tiles * n_kv_heads > (int64_t)room_tiles(tile) * grid) hw = n_kv_heads < 8 ? n_kv_heads : 8;
+    while (hw < 8 && hw < n_kv_heads && (int64_t)batch * n_kv_heads / hw > grid) hw *= 2;
     const int64_t groups = n_kv_heads / hw;
     const int cost = kPieceCost / hw > 1 ? kPieceCost / hw : 1;
     const int least = kMinTiles / (hw < kMinTiles ? hw : kMinTiles);

@@ -129,7 +129,7 @@ struct asrkf_ctx {
     void* small = nullptr;          // one allocation for every small array: those cleared by a reset
     size_t small_cleared = 0;       // come first, in so many bytes
     Status* status = nullptr;       // counters, flags and t_dev below
-    Status* status_host = nullptr;  // pinned copy
+    Status status_host{};           // its last copy
     float* ent_partial = nullptr;   // [B][kEntropySplitMax][3]
     int32_t* ent_ticket = nullptr;  // [B]
     unsigned long long* counters = nullptr;   // [0] listed_total, [1..3] recoveries, [5] rr,
@@ -240,7 +240,7 @@ void free_all(asrkf_ctx* ctx) {
                     ctx->row_owner, ctx->pop_buf, ctx->out_pos, ctx->out_row, ctx->in_pos, ctx->in_row,
                     ctx->hmask, ctx->hlast, ctx->seg_count};
     for (void* p : ptrs) if (p) (void)hipFree(p);
-    void* host[] = {ctx->khost, ctx->vhost, ctx->flags_host, ctx->status_host};
+    void* host[] = {ctx->khost, ctx->vhost, ctx->flags_host};
     for (void* p : host) if (p) (void)hipHostFree(p);
     if (ctx->side) (void)hipStreamDestroy(ctx->side);
     if (ctx->ev_lists) (void)hipEventDestroy(ctx->ev_lists);
@@ -521,8 +521,7 @@ asrkf_status asrkf_init(const asrkf_config* cfg, asrkf_ctx** out) {
 #undef ALLOC
 
     {
-        hipError_t he = hipEventCreateWithFlags(&ctx->ev_switch, hipEventDisableTiming);
-        if (he == hipSuccess) he = hipHostMalloc((void**)&ctx->status_host, sizeof(Status), hipHostMallocDefault);
+        const hipError_t he = hipEventCreateWithFlags(&ctx->ev_switch, hipEventDisableTiming);
         if (he != hipSuccess) {
             st = hip_fail(nullptr, he, "hipEventCreateWithFlags");
             free_all(ctx);
@@ -698,8 +697,8 @@ asrkf_status build_lists(asrkf_ctx* ctx, int forced_level, hipStream_t s) {
 asrkf_status check_overflow(asrkf_ctx* ctx, bool synced) {
     int32_t f[2] = {0, 0};
     if (synced) {
-        f[0] = ctx->status_host->flags[0];
-        f[1] = ctx->status_host->flags[1];
+        f[0] = ctx->status_host.flags[0];
+        f[1] = ctx->status_host.flags[1];
     } else {
         if (!ctx->spill) return ASRKF_OK;
         f[0] = ((volatile int32_t*)ctx->flags_host)[0];
@@ -914,10 +913,10 @@ namespace {
 // started, so a step in progress is not yet complete).
 asrkf_status sync_ctx(asrkf_ctx* ctx) {
     // the status block comes back behind the queued work: one wait for both
-    HIP_OK(ctx, hipMemcpyAsync(ctx->status_host, ctx->status, sizeof(Status), hipMemcpyDeviceToHost, ctx->last_stream));
+    HIP_OK(ctx, hipMemcpyAsync(&ctx->status_host, ctx->status, sizeof(Status), hipMemcpyDeviceToHost, ctx->last_stream));
     HIP_OK(ctx, hipStreamSynchronize(ctx->last_stream));
     if (ctx->side) HIP_OK(ctx, hipStreamSynchronize(ctx->side));
-    const int completed = ctx->status_host->t - (ctx->next_layer != 0 ? 1 : 0);
+    const int completed = ctx->status_host.t - (ctx->next_layer != 0 ? 1 : 0);
     if (completed > ctx->t) ctx->t = completed;
     return ASRKF_OK;
 }
@@ -953,7 +952,7 @@ asrkf_status asrkf_stats(asrkf_ctx* ctx, asrkf_stats_t* out) {
     const size_t inst = (size_t)ctx->state_layers * c.batch;
     // with token scope one list serves every layer: count it once per layer
     const int64_t per_list = ctx->token_scope ? c.n_layers : 1;
-    const unsigned long long* cnt = ctx->status_host->counters;
+    const unsigned long long* cnt = ctx->status_host.counters;
     std::vector<int32_t> na(inst);
     HIP_OK(ctx, hipMemcpy(na.data(), ctx->n_active, inst * 4, hipMemcpyDeviceToHost));
     memset(out, 0, sizeof *out);

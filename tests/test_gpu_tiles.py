@@ -74,8 +74,8 @@ def test_tile_and_workgroup_edges(layout):
 @pytest.mark.parametrize("scope", ["layer", "token"])
 @pytest.mark.parametrize("batch", [64, 65, 130])
 def test_many_sequences(batch, scope, relevance):
-    """64 sequences are planned in registers, more in LDS; 130 x 8 pairs give
-    every workgroup the eight KV heads of a sequence together."""
+    """64 sequences are planned in registers, more in LDS; with 8 KV heads they
+    give a workgroup two, four and eight heads of a sequence together."""
     w = gen.Workload(name=f"tiles-b{batch}-{scope}-{relevance}", seed=gen.SEED + 202, n_layers=2,
                      batch=batch, n_q_heads=16, n_kv_heads=8, head_dim=64, dtype="bf16",
                      prefill=[900 if b == 3 else (0 if b % 7 == 2 else 5 + 13 * b % 90) for b in range(batch)],
