@@ -372,6 +372,13 @@ struct Row {
 template <bool BF16, int G>
 constexpr int parts_apart() { return BF16 && G == 8 ? 1 : 0; }
 
+// The weight of a state with maximum m under the common maximum M.  A state
+// without a finite score counts nothing, but its sums are folded all the same:
+// they are zero, or NaN where a score was, which the result has to show.
+__device__ __forceinline__ float state_weight(float m, float M) {
+    return m == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(m - M);
+}
+
 // (L, o) += wgt * (l, v)
 __device__ __forceinline__ void fold(float& L, floatx4& o, float wgt, float l, floatx4 v) {
     L = fmaf(wgt, l, L);
@@ -728,11 +735,12 @@ attention_kernel(AttnArgs a) {
                     }
             }
             float p[NBLK][4];
+            const float mr = m == -INFINITY ? 0.f : m;    // a score of -inf weighs 0, also before any other
 #pragma unroll
             for (int blk = 0; blk < NBLK; ++blk)
 #pragma unroll
                 for (int i = 0; i < 4; ++i) {
-                    p[blk][i] = __builtin_amdgcn_exp2f(y[blk][i] - m);
+                    p[blk][i] = __builtin_amdgcn_exp2f(y[blk][i] - mr);
                     l += p[blk][i];
                 }
             if constexpr (BF16) {
@@ -855,7 +863,7 @@ attention_kernel(AttnArgs a) {
             floatx4 o = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
             for (int j = 0; j < kWaves; ++j) {
-                if (mw[j] != -INFINITY) fold(L, o, __builtin_amdgcn_exp2f(mw[j] - M), lw[j], ow[j]);
+                if (j < nwt) fold(L, o, state_weight(mw[j], M), lw[j], ow[j]);
             }
             if (n_parts == 1) {
                 fin.template write<D>(hh, d, M, L, o);
@@ -909,13 +917,13 @@ attention_kernel(AttnArgs a) {
 #pragma unroll
                         for (int u = 0; u < kPass; ++u)
                             if (k + u * kSlotGroups < n_parts) Mn = fmaxf(Mn, pml[u][0]);
-                        const float sc = M == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(M - Mn);
+                        const float sc = state_weight(M, Mn);
                         L *= sc;
                         o *= sc;
 #pragma unroll
                         for (int u = 0; u < kPass; ++u)
                             if (k + u * kSlotGroups < n_parts)
-                                fold(L, o, __builtin_amdgcn_exp2f(pml[u][0] - Mn), pml[u][1], po[u]);
+                                fold(L, o, state_weight(pml[u][0], Mn), pml[u][1], po[u]);
                         M = Mn;
                     }
                     if constexpr (kSlotGroups > 1) {
@@ -929,15 +937,13 @@ attention_kernel(AttnArgs a) {
 #pragma unroll
                             for (int k = 1; k < kSlotGroups; ++k)
                                 Mt = fmaxf(Mt, fold_ml(threadIdx.x + k * kFoldThreads)[0]);
-                            const float s0 = __builtin_amdgcn_exp2f(M - Mt);
+                            const float s0 = state_weight(M, Mt);
                             L *= s0;
                             o *= s0;
 #pragma unroll
                             for (int k = 1; k < kSlotGroups; ++k) {
                                 const int src = threadIdx.x + k * kFoldThreads;
-                                const float mk = fold_ml(src)[0];
-                                if (mk != -INFINITY)
-                                    fold(L, o, __builtin_amdgcn_exp2f(mk - Mt), fold_ml(src)[1], *fold_o(src));
+                                fold(L, o, state_weight(fold_ml(src)[0], Mt), fold_ml(src)[1], *fold_o(src));
                             }
                             M = Mt;
                         }

@@ -188,3 +188,69 @@ def test_prompt_alignment(gpu, dtype, offset):
         finally:
             A.asrkf_destroy(ctx)
     np.testing.assert_array_equal(outs[0], outs[1])
+
+
+def _one_step(gpu, layout, batch, n, poison):
+    """One step over `batch` sequences of n prompt tokens; poison(K) edits the
+    keys [batch][n + 1][Hkv][D] first (the last row is the new token's).  Query
+    entries 5 are positive.  Returns q, K, V and the output, in 64 bits."""
+    torch = gpu
+    import paper_2512_11221_amd as A
+    lay = LAYOUTS[layout]
+    Hq, Hkv, D = lay["n_q_heads"], lay["n_kv_heads"], lay["head_dim"]
+    dt = torch.bfloat16 if lay["dtype"] == "bf16" else torch.float32
+    g = torch.Generator(device="cuda").manual_seed(17)
+    K = torch.randn((batch, n + 1, Hkv, D), generator=g, device="cuda", dtype=dt)
+    V = torch.randn((batch, n + 1, Hkv, D), generator=g, device="cuda", dtype=dt)
+    q = torch.randn((batch, Hq, D), generator=g, device="cuda", dtype=dt)
+    q[..., 5] = q[..., 5].abs() + 0.125
+    poison(K)
+    out = torch.empty((batch, Hq, D), device="cuda")
+    ctx = A.asrkf_init(A.make_config(1, batch, Hq, Hkv, D, n + 2, 16, 0.0, 2.0, 16, dtype=lay["dtype"]))
+    try:
+        for b in range(batch):
+            A.asrkf_prefill(ctx, 0, b, K[b], V[b], n)
+        A.asrkf_decode_step(ctx, 0, q, K[:, n].contiguous(), V[:, n].contiguous(), out)
+        return [x.double().cpu() for x in (q, K, V, out)]
+    finally:
+        A.asrkf_destroy(ctx)
+
+
+# where the keys of KV head 0 of the last sequence are not finite: the new token
+# alone in its tile; whole tiles, so that one wave or one workgroup sees nothing
+# else; a single one among others
+POISONED = {"new": (1, 576, [576]), "tiles": (1, 600, range(64, 256)), "first": (1, 600, range(0, 192)),
+            "one": (1, 600, [10]), "batch": (66, 64, [64])}
+
+
+@pytest.mark.parametrize("where", sorted(POISONED))
+@pytest.mark.parametrize("layout", ["bf16-128-g4", "bf16-128-g8", "bf16-64-g1", "bf16-256-g2", "f32-64-g4"])
+def test_nan_keys(gpu, layout, where):
+    """A score that is no number makes its head's outputs NaN, wherever the token
+    falls among the waves and workgroups, and no other head's."""
+    batch, n, rows = POISONED[where]
+
+    def poison(K):
+        K[-1, list(rows), 0, 5] = math.nan
+    q, K, V, out = _one_step(gpu, layout, batch, n, poison)
+    G = q.shape[1] // K.shape[2]
+    assert out[-1, :G].isnan().all()
+    assert out[-1, G:].isfinite().all() and out[:-1].isfinite().all()
+
+
+@pytest.mark.parametrize("where", sorted(POISONED))
+@pytest.mark.parametrize("layout", ["bf16-128-g4", "bf16-128-g8", "bf16-64-g1", "f32-64-g4"])
+def test_scores_of_minus_infinity(gpu, layout, where):
+    """A score of -inf weighs nothing, also where a wave or a workgroup sees only
+    such scores."""
+    torch = gpu
+    batch, n, rows = POISONED[where]
+
+    def poison(K):
+        K[-1, list(rows), 0, 5] = -math.inf
+    q, K, V, out = _one_step(gpu, layout, batch, n, poison)
+    G, D = q.shape[1] // K.shape[2], q.shape[2]
+    for h in range(q.shape[1]):
+        x = K[-1, :, h // G] @ q[-1, h] / math.sqrt(D)
+        ref = torch.softmax(x, 0) @ V[-1, :, h // G]
+        assert float((out[-1, h] - ref).abs().max()) <= OUT_TOL
