@@ -69,9 +69,6 @@ constexpr int kAgentScope = 16;
 // there return zeros and stores are dropped, without a memory access, so
 // masked lanes cost nothing and the compiler counts every wait exactly
 constexpr int kNowhere = (int)0x80000000;
-// a wave rescales its sums when a score passes the running maximum by more
-// than this (log2 units): weights stay below 2^6, far from any fp32 limit
-constexpr float kMaxLag = 6.f;
 
 __device__ __forceinline__ int wave_uniform(int x) { return __builtin_amdgcn_readfirstlane(x); }
 
@@ -714,7 +711,9 @@ attention_kernel(AttnArgs a) {
             for (int blk = 0; blk < NBLK; ++blk)
 #pragma unroll
                 for (int i = 0; i < 4; ++i) top = fmaxf(top, y[blk][i]);
-            if (__any(top > m + kMaxLag)) {
+            // any new maximum rescales the sums: no weight passes 1, so the sums stay
+            // within the tokens' number times the largest value
+            if (__any(top > m)) {
                 top = fmaxf(top, __shfl_xor(top, 16));
                 top = fmaxf(top, __shfl_xor(top, 32));
                 const float mn = fmaxf(m, top);

@@ -254,3 +254,37 @@ def test_scores_of_minus_infinity(gpu, layout, where):
         x = K[-1, :, h // G] @ q[-1, h] / math.sqrt(D)
         ref = torch.softmax(x, 0) @ V[-1, :, h // G]
         assert float((out[-1, h] - ref).abs().max()) <= OUT_TOL
+
+
+@pytest.mark.parametrize("layout", ["bf16-128-g4", "bf16-128-g8", "bf16-64-g1", "bf16-256-g2", "f32-64-g4"])
+def test_values_near_the_largest(gpu, layout):
+    """Values of 2^125 on tokens that score 5.5 (log2 units) above everything
+    before them, one such token per dimension: with weights of at most 1 every sum
+    stays below 2^126.  Bound: relative, as for ordinary values."""
+    torch = gpu
+    import paper_2512_11221_amd as A
+    lay = LAYOUTS[layout]
+    Hq, Hkv, D = lay["n_q_heads"], lay["n_kv_heads"], lay["head_dim"]
+    dt = torch.bfloat16 if lay["dtype"] == "bf16" else torch.float32
+    n, batch = 1200, 66
+    g = torch.Generator(device="cuda").manual_seed(19)
+    K = torch.zeros((n + 1, Hkv, D), device="cuda")
+    V = torch.randn((n + 1, Hkv, D), generator=g, device="cuda").to(dt).float()
+    high = 600 + 9 * torch.arange(64, device="cuda")
+    K[high, :, 0] = 5.5 * math.sqrt(D) / math.log2(math.e)
+    V[high, :, torch.arange(64, device="cuda")] = 2.0 ** 125
+    K, V = K.to(dt), V.to(dt)
+    q = torch.zeros((batch, Hq, D), device="cuda", dtype=dt)
+    q[..., 0] = 1.0
+    out = torch.empty((batch, Hq, D), device="cuda")
+    ctx = A.asrkf_init(A.make_config(1, batch, Hq, Hkv, D, n + 2, 16, 0.0, 2.0, 16, dtype=lay["dtype"]))
+    try:
+        for b in range(batch):
+            A.asrkf_prefill(ctx, 0, b, K, V, n)
+        new = [x[n:].expand(batch, Hkv, D).contiguous() for x in (K, V)]
+        A.asrkf_decode_step(ctx, 0, q, new[0], new[1], out)
+        w = torch.softmax(K[:, 0, 0].double() / math.sqrt(D), 0)
+        ref = torch.einsum("n,nhd->hd", w, V.double()).repeat_interleave(Hq // Hkv, 0)
+        assert float(((out.double() - ref) / ref.abs().clamp_min(1.0)).abs().max()) <= 1e-5
+    finally:
+        A.asrkf_destroy(ctx)
