@@ -36,6 +36,10 @@
  *    call queues nothing until the graph is replayed.  The host learns of
  *    replayed steps at its next waiting call (asrkf_stats, asrkf_get_state,
  *    ...), which the caller makes before any further uncaptured decode_step.
+ *    On a context with captured calls the waiting calls wait for replays on
+ *    the default stream, on streams that synchronize with it, and on the
+ *    stream of the context's last call; the caller waits for a replay on any
+ *    other (non-blocking) stream first.
  *    A replayed step that takes a sequence past max_ctx positions is caught
  *    on the device (the end-of-step rebuild is skipped, no access goes out
  *    of bounds) and reported as ECAPACITY by the next waiting call.  Capture

@@ -183,6 +183,7 @@ struct asrkf_ctx {
     bool timing = false;
     hipStream_t last_stream = nullptr;  // stream of the last call that queued work
     bool queued = false;                // some call has queued work on last_stream
+    bool captured = false;              // some call was captured: replays may run on other streams
     hipEvent_t ev_switch = nullptr;     // orders a call on a new stream after last_stream
     std::vector<std::pair<hipEvent_t, hipEvent_t>> ev_used, ev_free;
     double attn_ms_done = 0.0;
@@ -351,9 +352,10 @@ hipError_t clear_state(asrkf_ctx* ctx, hipStream_t s) {
     return launch_clear(a, s);
 }
 
-void mark_queued(asrkf_ctx* ctx, hipStream_t s) {
+void mark_queued(asrkf_ctx* ctx, hipStream_t s, bool capture) {
     ctx->last_stream = s;
     ctx->queued = true;
+    if (capture) ctx->captured = true;
 }
 
 }  // namespace
@@ -580,7 +582,7 @@ asrkf_status asrkf_prefill(asrkf_ctx* ctx, int32_t layer, int32_t seq, const voi
     HIP_OK(ctx, launch_prefill(p, s));
     ctx->prefilled[seq] = 1;
     ctx->plen_host[seq] = n_tokens;
-    mark_queued(ctx, s);
+    mark_queued(ctx, s, capturing(s));
     return ASRKF_OK;
 }
 
@@ -752,7 +754,7 @@ asrkf_status decode_step_impl(asrkf_ctx* ctx, int32_t layer, const void* q, cons
     st = check_overflow(ctx, false);
     if (st != ASRKF_OK) return st;
     HIP_OK(ctx, follow_last_stream(ctx, s));
-    mark_queued(ctx, s);
+    mark_queued(ctx, s, capture);
     if (layer == 0) {
         attention_layout(ctx->plen_host.data(), c.batch, t, c.n_kv_heads, (int)(c.head_dim * ctx->esz), ctx->grid,
                          &ctx->heads_per_group, &ctx->launch);
@@ -854,11 +856,12 @@ asrkf_status asrkf_restore(asrkf_ctx* ctx, const float* logits, int32_t mode, vo
         return fail(ASRKF_ESTATE, "restore before decode_step of every layer (next layer %d of %d)",
                     ctx->next_layer, c.n_layers);
     hipStream_t s = static_cast<hipStream_t>(stream);
-    if (ctx->spill && capturing(s)) return fail(ASRKF_ESTATE, "spill-mode steps cannot be captured in a graph");
+    const bool capture = capturing(s);
+    if (ctx->spill && capture) return fail(ASRKF_ESTATE, "spill-mode steps cannot be captured in a graph");
     st = check_overflow(ctx, false);
     if (st != ASRKF_OK) return st;
     HIP_OK(ctx, follow_last_stream(ctx, s));
-    mark_queued(ctx, s);
+    mark_queued(ctx, s, capture);
     int forced;
     EntropyArgs e{};
     if (logits) {
@@ -896,7 +899,7 @@ asrkf_status asrkf_restore(asrkf_ctx* ctx, const float* logits, int32_t mode, vo
     HIP_OK(ctx, launch_monitor(logits ? &e : nullptr, v, s));
     // a captured step runs only when replayed: the host learns of it from the
     // device step counter at its next wait
-    if (!capturing(s)) ctx->t += 1;
+    if (!capture) ctx->t += 1;
     ctx->next_layer = 0;
     return build_lists(ctx, forced, s);
 }
@@ -912,9 +915,16 @@ namespace {
 // counter: after the wait the host adopts it (the counter counts steps
 // started, so a step in progress is not yet complete).
 asrkf_status sync_ctx(asrkf_ctx* ctx) {
-    // the status block comes back behind the queued work: one wait for both
-    HIP_OK(ctx, hipMemcpyAsync(&ctx->status_host, ctx->status, sizeof(Status), hipMemcpyDeviceToHost, ctx->last_stream));
-    HIP_OK(ctx, hipStreamSynchronize(ctx->last_stream));
+    if (!ctx->captured) {
+        // the status block comes back behind the queued work: one wait for both
+        HIP_OK(ctx, hipMemcpyAsync(&ctx->status_host, ctx->status, sizeof(Status), hipMemcpyDeviceToHost, ctx->last_stream));
+        HIP_OK(ctx, hipStreamSynchronize(ctx->last_stream));
+    } else {
+        // last_stream may be the stream of the capture, where the replays do not run: the
+        // blocking copy is ordered after the default stream and every stream that follows it
+        HIP_OK(ctx, hipStreamSynchronize(ctx->last_stream));
+        HIP_OK(ctx, hipMemcpy(&ctx->status_host, ctx->status, sizeof(Status), hipMemcpyDeviceToHost));
+    }
     if (ctx->side) HIP_OK(ctx, hipStreamSynchronize(ctx->side));
     const int completed = ctx->status_host.t - (ctx->next_layer != 0 ? 1 : 0);
     if (completed > ctx->t) ctx->t = completed;

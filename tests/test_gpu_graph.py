@@ -228,3 +228,75 @@ def test_replays_past_max_ctx_are_refused_on_the_device():
         assert e.value.code == L.ECAPACITY and "max_ctx" in str(e.value)
     finally:
         A.asrkf_destroy(ctx)
+
+
+def test_waiting_calls_wait_for_replays():
+    """asrkf_stats, asrkf_get_state, asrkf_get_seq and asrkf_reset straight after a
+    run of replays on the default stream, with no synchronization by the caller:
+    they see every replayed step, and a reset context runs like a new one."""
+    import torch
+    import paper_2512_11221_amd as A
+    w = _workload(n_layers=4, prefill=[3000, 2500], steps=40)
+    s_cold, s_hot = gen.hh_relevance_bounds(w)
+    assert s_cold < w.tau - H.MARGIN and s_hot > w.tau + H.MARGIN
+    warm, burst = 2, 6
+    keys = ("step", "attended_total", "active_positions", "total_positions", "recoveries", "rr_requests")
+    buf = _Static(w)
+
+    def look(ctx):
+        stats = A.asrkf_stats(ctx)
+        states = [A.asrkf_get_state(ctx, l, b, w.max_ctx) for l in range(w.n_layers) for b in range(w.batch)]
+        return {k: stats[k] for k in keys}, states, A.asrkf_get_seq(ctx, 1)
+
+    def same(x, y):
+        assert x[0] == y[0] and x[2] == y[2]
+        for g, o in zip(x[1], y[1]):
+            for f in ("unfreeze", "count", "frozen", "active"):
+                np.testing.assert_array_equal(g[f], o[f])
+
+    # the reference: the same inputs at every step, run eagerly
+    ctx, inp = _open(A, w)
+    buf.load(w, inp, 1)
+    ref, ref_out = {}, {}
+    try:
+        for t in range(1, warm + 3 * burst + 1):
+            buf.step(A, ctx, w)
+            torch.cuda.synchronize()
+            ref[t], ref_out[t] = look(ctx), buf.out.clone()
+    finally:
+        A.asrkf_destroy(ctx)
+
+    ctx, _ = _open(A, w)
+    try:
+        torch.cuda.synchronize()
+        for _ in range(warm):
+            buf.step(A, ctx, w)
+        g = _capture(torch, A, ctx, w, buf)
+        t = warm
+        for first in ("stats", "state"):
+            for _ in range(burst):
+                g.replay()
+            t += burst
+            if first == "stats":
+                same(look(ctx), ref[t])
+            else:
+                st = A.asrkf_get_state(ctx, 0, 0, w.max_ctx)
+                assert st["n"] == w.prefill[0] + t
+                for f in ("unfreeze", "count", "frozen", "active"):
+                    np.testing.assert_array_equal(st[f], ref[t][1][0][f])
+            assert torch.equal(buf.out, ref_out[t])
+        for _ in range(burst):
+            g.replay()
+        A.asrkf_reset(ctx)                             # waits for the replays, then clears
+        assert torch.equal(buf.out, ref_out[t + burst])
+        for l in range(w.n_layers):
+            for b in range(w.batch):
+                K, V = inp.prompt(l, b)
+                A.asrkf_prefill(ctx, l, b, H._dev(K, w.dtype), H._dev(V, w.dtype), len(K))
+        torch.cuda.synchronize()
+        for t in range(1, warm + 1):
+            buf.step(A, ctx, w)
+            same(look(ctx), ref[t])
+            assert torch.equal(buf.out, ref_out[t])
+    finally:
+        A.asrkf_destroy(ctx)
