@@ -528,7 +528,7 @@ attention_kernel(AttnArgs a) {
         const int32_t* list_b = (a.spill ? a.list_row : a.list) + (size_t)b * a.cap;
         const auto rl = buffer(list_b, a.cap * 4);
         const int planes = rel_abs ? groups : a.Hq;
-        const auto rr = buffer(a.rel + (size_t)b * a.planes * a.cap, planes * a.cap * 4);
+        const auto rr = buffer(a.rel + (size_t)b * a.planes * a.rel_cap, planes * a.rel_cap * 4);
         // Load j of a tile takes the tokens j * kPer .. j * kPer + kPer - 1, so that in a
         // dense list one instruction reads 1 KiB in a row.  Lane i of a row of 16 lanes
         // holds the list entry that the row's lanes need in load i (a row broadcast
@@ -577,13 +577,13 @@ attention_kernel(AttnArgs a) {
                     for (int h = 0; h < hw; ++h)
                         v += *reinterpret_cast<const floatx4*>(
                             tiles + (h + hw * turn) * R::kWaveLds + R::kTileLds + (idx * kTile + o * 4) * 4);
-                    at = gi * a.cap + (c0 + row) * kTile + o * 4;
+                    at = gi * a.rel_cap + (c0 + row) * kTile + o * 4;
                 } else {
                     const int c = row % wide, idx = row / wide % per_wave, wv = row / wide / per_wave;
                     const int tile = c0 + wv / hw + idx * nwt;
                     v = *reinterpret_cast<const floatx4*>(tiles + wv * R::kWaveLds + R::kTileLds +
                                                           ((idx * wide + c) * kTile + o * 4) * 4);
-                    at = ((gi * hw + wv % hw) * G + c) * a.cap + tile * kTile + o * 4;
+                    at = ((gi * hw + wv % hw) * G + c) * a.rel_cap + tile * kTile + o * 4;
                     if (tile >= c1) at = kNowhere / 4;
                 }
                 __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(uintx4, v), rr, at * 4, 0, kStreamPolicy);

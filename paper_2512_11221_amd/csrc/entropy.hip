@@ -174,21 +174,26 @@ constexpr int kEntries = 4 * kThreads;        // list entries per verdict workgr
 constexpr int kPlaneGroup = 4;
 
 __device__ void verdict_block(const VerdictArgs& v, int chunk, int inst) {
-    const int n = v.n_active[inst];
+    const int n = min(v.n_active[inst], v.rel_cap);      // more only where device rows ran out
     const int i0 = chunk * kEntries + 4 * threadIdx.x;
     if (i0 >= n) return;
     const int b = inst % v.B, state = inst / v.B;
     float s[4] = {0.f, 0.f, 0.f, 0.f};
+    float4* sum = reinterpret_cast<float4*>(v.sum + (size_t)b * v.rel_cap + i0);
+    if (v.add_sum) {
+        const float4 before = *sum;
+        s[0] = before.x; s[1] = before.y; s[2] = before.z; s[3] = before.w;
+    }
     const int4 pos = *reinterpret_cast<const int4*>(v.list + (size_t)inst * v.cap + i0);
     for (int l = 0; l < v.layers_summed; ++l) {
         const size_t li = (size_t)(state + l) * v.B + b;          // the layer's instance
-        const float* rel = v.rel + li * v.planes * v.cap + i0;
+        const float* rel = v.rel + li * v.planes * v.rel_cap + i0;
         const float* norm = v.norm + li * v.planes * 2;
         for (int p0 = 0; p0 < v.used; p0 += kPlaneGroup) {
             float4 x[kPlaneGroup];
 #pragma unroll
             for (int k = 0; k < kPlaneGroup; ++k)
-                x[k] = *reinterpret_cast<const float4*>(rel + (size_t)min(p0 + k, v.used - 1) * v.cap);
+                x[k] = *reinterpret_cast<const float4*>(rel + (size_t)min(p0 + k, v.used - 1) * v.rel_cap);
 #pragma unroll
             for (int k = 0; k < kPlaneGroup; ++k) {
                 if (p0 + k < v.used) {
@@ -207,6 +212,10 @@ __device__ void verdict_block(const VerdictArgs& v, int chunk, int inst) {
                 }
             }
         }
+    }
+    if (v.keep_sum) {
+        *sum = make_float4(s[0], s[1], s[2], s[3]);
+        return;
     }
     uint8_t* flag = v.flag + (size_t)inst * v.cap;
     const int p[4] = {pos.x, pos.y, pos.z, pos.w};
@@ -227,7 +236,7 @@ monitor_kernel(EntropyArgs e, VerdictArgs v, int entropy_blocks, int chunks) {
 
 hipError_t launch_monitor(const EntropyArgs* e, const VerdictArgs& v, hipStream_t s) {
     const int64_t entropy_blocks = e ? (int64_t)e->split * e->B : 0;
-    const int64_t chunks = (v.cap + kEntries - 1) / kEntries;
+    const int64_t chunks = (v.rel_cap + kEntries - 1) / kEntries;
     const int64_t blocks = entropy_blocks + chunks * v.states * v.B;
     if (blocks > (1 << 30)) return hipErrorInvalidValue;   // caches of that size exceed any device
     hipLaunchKernelGGL(monitor_kernel, dim3((unsigned)blocks), dim3(kThreads), 0, s,

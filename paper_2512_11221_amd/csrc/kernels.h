@@ -58,7 +58,7 @@ struct AttnArgs {
     const int32_t* list_row;  // layer base, [B][cap] device row of each listed position
                               // (spill mode only; in resident mode the row is the position)
     const int32_t* n_active;  // layer base, [B]
-    float* rel;               // layer base, [B][planes][cap] relevance of the list entries (written):
+    float* rel;               // layer base, [B][planes][rel_cap] relevance of the list entries (written):
                               // the first Hkv / heads_per_group planes hold |q.k| summed over a head
                               // group's query heads (Eq. 2); or Hq planes of logits
                               // q.k * log2(e)/sqrt(D) (softmax weights)
@@ -71,6 +71,7 @@ struct AttnArgs {
     float* norm;              // softmax weights: [B][Hq][2] (max, sum) (written), or null
     int32_t B, cap, Hq, Hkv;
     int32_t planes;           // plane stride of a sequence
+    int32_t rel_cap;          // entries of a plane (a multiple of 64)
     int32_t grid;             // workgroups the work is dealt to (a launch may have fewer or more)
     int32_t heads_per_group;  // KV heads a workgroup takes together (a power of two dividing Hkv)
     int32_t pool_rows;        // device rows per sequence (cap in resident mode)
@@ -83,16 +84,18 @@ struct AttnArgs {
 // attended position, bit 0 set where s_j < tau (Eq. 2, or the mean softmax
 // weight), bit 1 where s_j lies within the debug margin of tau.
 struct VerdictArgs {
-    const float* rel;         // [L][B][planes][cap] by list entry
-    const float* norm;        // softmax weights: [L][B][Hq][2]
+    const float* rel;         // [layers][B][planes][rel_cap] by list entry, of the layers judged
+    const float* norm;        // softmax weights: [layers][B][Hq][2]
     const int32_t* list;      // [states][B][cap]
     const int32_t* n_active;  // [states][B]
     uint8_t* flag;            // [states][B][cap] by position (written)
-    int32_t B, cap;
+    float* sum;               // token scope: [B][rel_cap] sums over the layers judged by earlier launches
+    int32_t B, cap, rel_cap;
     int32_t planes, used;     // plane stride of a sequence, planes that hold values
     int32_t softmax;
-    int32_t states;           // layers with states of their own: L, or 1 (token scope)
-    int32_t layers_summed;    // 1, or L (token scope: the sum over every layer)
+    int32_t states;           // layers judged that have states of their own, or 1 (token scope)
+    int32_t layers_summed;    // 1, or the layers judged (token scope: they are summed)
+    int32_t add_sum, keep_sum;  // token scope: sum is added / is written instead of the flags
     float tau_sum;            // tau * Hq (* L): compared against the sum
     float margin_sum;         // debug margin * Hq (* L); 0: off
 };

@@ -8,8 +8,9 @@
 //   score flag      [L][B][cap]           uint8   s_j < tau at the current step (Eq. 2)
 //   active list     [L][B][cap]           int32   ascending positions for the step
 //   n_active        [L][B]                int32
-//   relevance       [L][B][planes][cap]   fp32    products of the attended tokens, by list
-//                                                 entry: planes = Hkv (Eq. 2) or Hq (softmax)
+//   relevance       [kept][B][planes][entries] fp32 products of the attended tokens, by list
+//                                                 entry: planes = Hkv (Eq. 2) or Hq (softmax),
+//                                                 of the layers whose verdicts are still due
 //   partials        [grid+B*Hkv][heads][D+2] fp32 split-K attention partials
 //   tickets         [B][Hkv]              int32   arrivals at a shared pair, zero between launches
 //   per sequence    prompt length, escalation, level, entropy, p_max
@@ -125,7 +126,10 @@ struct asrkf_ctx {
     float* part_ml = nullptr;
     int32_t* ticket = nullptr;      // [B][Hkv]
     int planes = 0;                 // relevance planes: n_kv_heads, or n_q_heads (softmax reading)
-    float* rel = nullptr;           // [L][B][planes][cap]
+    float* rel = nullptr;           // [rel_layers][B][planes][rel_cap]
+    int rel_layers = 0;             // layers whose planes are kept: their verdicts share a launch
+    int rel_cap = 0;                // list entries of a plane
+    float* rel_sum = nullptr;       // [B][rel_cap] token scope: sums of the layers before
     void* small = nullptr;          // one allocation for every small array: those cleared by a reset
     size_t small_cleared = 0;       // come first, in so many bytes
     Status* status = nullptr;       // counters, flags and t_dev below
@@ -237,7 +241,7 @@ asrkf_status dev_alloc(asrkf_ctx* ctx, T** p, size_t bytes) {
 
 void free_all(asrkf_ctx* ctx) {
     void* ptrs[] = {ctx->kpool, ctx->vpool, ctx->unfreeze, ctx->count, ctx->flag, ctx->list, ctx->small,
-                    ctx->part_acc, ctx->rel, ctx->row_of, ctx->on_host, ctx->list_row, ctx->last_row,
+                    ctx->part_acc, ctx->rel, ctx->rel_sum, ctx->row_of, ctx->on_host, ctx->list_row, ctx->last_row,
                     ctx->row_owner, ctx->pop_buf, ctx->out_pos, ctx->out_row, ctx->in_pos, ctx->in_row,
                     ctx->hmask, ctx->hlast, ctx->seg_count};
     for (void* p : ptrs) if (p) (void)hipFree(p);
@@ -445,7 +449,6 @@ asrkf_status asrkf_init(const asrkf_config* cfg, asrkf_ctx** out) {
         ALLOC(hmask, st_pos * 8);
         ALLOC(hlast, st_pos * 4);
     }
-    ALLOC(rel, per_pos * ctx->planes * 4);
     ctx->n_seg = compact_segments((int)st_inst, ctx->cap, ctx->spill, &ctx->seg_len);
     if (ctx->n_seg > 1) ALLOC(seg_count, st_inst * (ctx->n_seg + 1) * 32);   // spill mode: 8 counts per segment
     ALLOC(part_acc, part_heads(ctx) * c.head_dim * 4);
@@ -519,6 +522,23 @@ asrkf_status asrkf_init(const asrkf_config* cfg, asrkf_ctx** out) {
             delete ctx;
             return st;
         }
+    }
+    // Relevance planes.  A list names distinct device rows, so a plane has room for
+    // pool_rows entries.  The planes of as many layers are kept as take a 32nd of the
+    // cache (every layer's under Eq. 2, at most a 64th of it, and under the softmax
+    // reading with rows of 128 and four query heads per KV head), or 8 MiB; the verdicts
+    // of every rel_layers layers take a launch of their own.  Where that does not fit
+    // into the device's memory, one layer's do.
+    ctx->rel_cap = std::min(ctx->cap, (ctx->pool_rows + 63) / 64 * 64);
+    const size_t layer_planes = (size_t)c.batch * ctx->planes * ctx->rel_cap * 4;
+    const size_t kept = std::max(2 * pool_bytes / 32, (size_t)8 << 20) / layer_planes;
+    ctx->rel_layers = (int)std::min(std::max(kept, (size_t)1), (size_t)c.n_layers);
+    if (ctx->token_scope && c.n_layers > 1) ALLOC(rel_sum, (size_t)c.batch * ctx->rel_cap * 4);
+    if (hipMalloc((void**)&ctx->rel, layer_planes * ctx->rel_layers) != hipSuccess) {
+        (void)hipGetLastError();
+        ctx->rel = nullptr;
+        ctx->rel_layers = 1;
+        ALLOC(rel, layer_planes);
     }
 #undef ALLOC
 
@@ -722,6 +742,35 @@ asrkf_status check_overflow(asrkf_ctx* ctx, bool synced) {
 
 namespace {
 
+// The verdicts of the layers before layer_end whose planes are kept, and with e
+// the entropy monitors.
+hipError_t launch_verdicts(const asrkf_ctx* ctx, int layer_end, const EntropyArgs* e, hipStream_t s) {
+    const asrkf_config& c = ctx->cfg;
+    const int layer0 = (layer_end - 1) / ctx->rel_layers * ctx->rel_layers;
+    const size_t inst0 = (size_t)layer0 * c.batch, st0 = ctx->token_scope ? 0 : inst0;
+    VerdictArgs v{};
+    v.rel = ctx->rel;
+    v.norm = ctx->norm ? ctx->norm + inst0 * c.n_q_heads * 2 : nullptr;
+    v.list = ctx->list + st0 * ctx->cap;
+    v.n_active = ctx->n_active + st0;
+    v.flag = ctx->flag + st0 * ctx->cap;
+    v.sum = ctx->rel_sum;
+    v.B = c.batch;
+    v.cap = ctx->cap;
+    v.rel_cap = ctx->rel_cap;
+    v.planes = ctx->planes;
+    v.used = c.relevance == ASRKF_REL_SOFTMAX ? c.n_q_heads : c.n_kv_heads / ctx->heads_per_group;
+    v.softmax = c.relevance == ASRKF_REL_SOFTMAX ? 1 : 0;
+    v.states = ctx->token_scope ? 1 : layer_end - layer0;
+    v.layers_summed = ctx->token_scope ? layer_end - layer0 : 1;
+    v.add_sum = ctx->token_scope && layer0 > 0 ? 1 : 0;
+    v.keep_sum = ctx->token_scope && layer_end < c.n_layers ? 1 : 0;
+    const float scored_layers = (float)(ctx->token_scope ? c.n_layers : 1);
+    v.tau_sum = c.tau * scored_layers * (float)c.n_q_heads;
+    v.margin_sum = c.debug_margin * scored_layers * (float)c.n_q_heads;
+    return launch_monitor(e, v, s);
+}
+
 // decode_step with its split partials in the context's scratch, or (use_static)
 // in the static array, with no event of its own.
 asrkf_status decode_step_impl(asrkf_ctx* ctx, int32_t layer, const void* q, const void* k_new,
@@ -790,7 +839,8 @@ asrkf_status decode_step_impl(asrkf_ctx* ctx, int32_t layer, const void* q, cons
     a.n_active = ctx->n_active + st0;
     a.t_dev = layer == 0 ? ctx->t_dev : nullptr;
     a.rel_mode = c.relevance;
-    a.rel = ctx->rel + inst0 * ctx->planes * ctx->cap;
+    a.rel = ctx->rel + (size_t)(layer % ctx->rel_layers) * c.batch * ctx->planes * ctx->rel_cap;
+    a.rel_cap = ctx->rel_cap;
     a.part_acc = ctx->part_acc;
     a.part_ml = ctx->part_ml;
     a.ticket = ctx->ticket;
@@ -824,6 +874,9 @@ asrkf_status decode_step_impl(asrkf_ctx* ctx, int32_t layer, const void* q, cons
     HIP_OK(ctx, launch_attention(a, c.dtype == ASRKF_BF16, c.head_dim, ctx->group, ctx->launch, s,
                                  ev.first, ev.second));
     if (ev.first) ctx->ev_used.push_back(ev);
+    // the next layer overwrites the planes kept so far
+    if ((layer + 1) % ctx->rel_layers == 0 && layer + 1 < c.n_layers)
+        HIP_OK(ctx, launch_verdicts(ctx, layer + 1, nullptr, s));
 
     ctx->next_layer = layer + 1;
     return ASRKF_OK;
@@ -881,22 +934,7 @@ asrkf_status asrkf_restore(asrkf_ctx* ctx, const float* logits, int32_t mode, vo
     } else {
         forced = (mode >= ASRKF_SR && mode <= ASRKF_FR) ? (int)mode : 0;
     }
-    VerdictArgs v{};
-    v.rel = ctx->rel;
-    v.norm = ctx->norm;
-    v.list = ctx->list;
-    v.n_active = ctx->n_active;
-    v.flag = ctx->flag;
-    v.B = c.batch;
-    v.cap = ctx->cap;
-    v.planes = ctx->planes;
-    v.used = c.relevance == ASRKF_REL_SOFTMAX ? c.n_q_heads : c.n_kv_heads / ctx->heads_per_group;
-    v.softmax = c.relevance == ASRKF_REL_SOFTMAX ? 1 : 0;
-    v.states = ctx->state_layers;
-    v.layers_summed = ctx->token_scope ? c.n_layers : 1;
-    v.tau_sum = c.tau * (float)v.layers_summed * (float)c.n_q_heads;
-    v.margin_sum = c.debug_margin * (float)v.layers_summed * (float)c.n_q_heads;
-    HIP_OK(ctx, launch_monitor(logits ? &e : nullptr, v, s));
+    HIP_OK(ctx, launch_verdicts(ctx, c.n_layers, logits ? &e : nullptr, s));
     // a captured step runs only when replayed: the host learns of it from the
     // device step counter at its next wait
     if (!capture) ctx->t += 1;
