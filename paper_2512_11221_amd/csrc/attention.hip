@@ -369,12 +369,11 @@ struct Row {
 template <bool BF16, int G>
 constexpr int parts_apart() { return BF16 && G == 8 ? 1 : 0; }
 
-// The weight of a state with maximum m under the common maximum M.  A state
-// without a finite score counts nothing, but its sums are folded all the same:
-// they are zero, or NaN where a score was, which the result has to show.
-__device__ __forceinline__ float state_weight(float m, float M) {
-    return m == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(m - M);
-}
+// A maximum as the reference of exponents: 2^(x - reference(M)) is 0 for x = -inf,
+// also where no score above -inf came yet.  States without such a score are folded
+// like the others, with weight 0: their sums are zero, or NaN where a score was,
+// which the result has to show.
+__device__ __forceinline__ float reference(float M) { return M == -INFINITY ? 0.f : M; }
 
 // (L, o) += wgt * (l, v)
 __device__ __forceinline__ void fold(float& L, floatx4& o, float wgt, float l, floatx4 v) {
@@ -413,6 +412,14 @@ __device__ __forceinline__ float add_rows16(float a, float b) {
 __device__ __forceinline__ float add_halves(float a, float b) {
     const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(a), __float_as_uint(b), false, false);
     return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
+
+// the maximum over the lanes of a column (its four rows of 16 lanes)
+__device__ __forceinline__ float column_max(float v) {
+    const auto a = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    v = fmaxf(__uint_as_float(a[0]), __uint_as_float(a[1]));
+    const auto b = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    return fmaxf(__uint_as_float(b[0]), __uint_as_float(b[1]));
 }
 
 // A wave's accumulators as [G][kMergeStride] sums in LDS.  Row 4 q4 + i, column
@@ -714,17 +721,21 @@ attention_kernel(AttnArgs a) {
             // any new maximum rescales the sums: no weight passes 1, so the sums stay
             // within the tokens' number times the largest value
             if (__any(top > m)) {
-                top = fmaxf(top, __shfl_xor(top, 16));
-                top = fmaxf(top, __shfl_xor(top, 32));
-                const float mn = fmaxf(m, top);
+                const float mn = fmaxf(m, column_max(top));
                 const float sc = m < mn ? __builtin_amdgcn_exp2f(m - mn) : 1.f;
                 l *= sc;
                 m = mn;
-                float row_sc[4];
-#pragma unroll
-                for (int i = 0; i < 4; ++i) {     // the scale of row 4 q4 + i: head (4 q4 + i) % G
-                    row_sc[i] = __shfl(sc, (q4 * 4 + i) % G);
-                }
+                float row_sc[4];                  // the scale of row 4 q4 + i: head (4 q4 + i) % G
+                unroll<4>([&](auto I) __attribute__((always_inline)) {
+                    constexpr int i = decltype(I)::value;
+                    const int x = row_bcast<i % G>(__float_as_int(sc));
+                    if constexpr (G == 8) {
+                        const int y = row_bcast<4 + i>(__float_as_int(sc));
+                        row_sc[i] = __int_as_float(q4 & 1 ? y : x);
+                    } else {
+                        row_sc[i] = __int_as_float(x);
+                    }
+                });
 #pragma unroll
                 for (int k = 0; k < NB; ++k)
 #pragma unroll
@@ -734,7 +745,7 @@ attention_kernel(AttnArgs a) {
                     }
             }
             float p[NBLK][4];
-            const float mr = m == -INFINITY ? 0.f : m;    // a score of -inf weighs 0, also before any other
+            const float mr = reference(m);
 #pragma unroll
             for (int blk = 0; blk < NBLK; ++blk)
 #pragma unroll
@@ -858,11 +869,12 @@ attention_kernel(AttnArgs a) {
             float M = mw[0];
 #pragma unroll
             for (int j = 1; j < kWaves; ++j) M = fmaxf(M, mw[j]);
+            const float Mr = reference(M);
             float L = 0.f;
             floatx4 o = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
             for (int j = 0; j < kWaves; ++j) {
-                if (j < nwt) fold(L, o, state_weight(mw[j], M), lw[j], ow[j]);
+                if (j < nwt) fold(L, o, __builtin_amdgcn_exp2f(mw[j] - Mr), lw[j], ow[j]);
             }
             if (n_parts == 1) {
                 fin.template write<D>(hh, d, M, L, o);
@@ -916,13 +928,13 @@ attention_kernel(AttnArgs a) {
 #pragma unroll
                         for (int u = 0; u < kPass; ++u)
                             if (k + u * kSlotGroups < n_parts) Mn = fmaxf(Mn, pml[u][0]);
-                        const float sc = state_weight(M, Mn);
+                        const float Mr = reference(Mn), sc = __builtin_amdgcn_exp2f(M - Mr);
                         L *= sc;
                         o *= sc;
 #pragma unroll
                         for (int u = 0; u < kPass; ++u)
                             if (k + u * kSlotGroups < n_parts)
-                                fold(L, o, state_weight(pml[u][0], Mn), pml[u][1], po[u]);
+                                fold(L, o, __builtin_amdgcn_exp2f(pml[u][0] - Mr), pml[u][1], po[u]);
                         M = Mn;
                     }
                     if constexpr (kSlotGroups > 1) {
@@ -936,13 +948,13 @@ attention_kernel(AttnArgs a) {
 #pragma unroll
                             for (int k = 1; k < kSlotGroups; ++k)
                                 Mt = fmaxf(Mt, fold_ml(threadIdx.x + k * kFoldThreads)[0]);
-                            const float s0 = state_weight(M, Mt);
+                            const float Mr = reference(Mt), s0 = __builtin_amdgcn_exp2f(M - Mr);
                             L *= s0;
                             o *= s0;
 #pragma unroll
                             for (int k = 1; k < kSlotGroups; ++k) {
                                 const int src = threadIdx.x + k * kFoldThreads;
-                                fold(L, o, state_weight(fold_ml(src)[0], Mt), fold_ml(src)[1], *fold_o(src));
+                                fold(L, o, __builtin_amdgcn_exp2f(fold_ml(src)[0] - Mr), fold_ml(src)[1], *fold_o(src));
                             }
                             M = Mt;
                         }
