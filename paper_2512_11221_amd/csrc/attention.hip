@@ -39,7 +39,13 @@
 // lanes.  fp32 rows use the fp32 matrix instruction.  bf16 rows keep fp32
 // weights: the repeated columns carry p's leading, middle and trailing 8
 // mantissa bits as three bf16 rows (exact: p = hi + mid + lo), summed in fp32
-// when the waves are merged.
+// when the waves are merged.  With eight query heads the sixteen rows hold two
+// parts, so a tile takes two passes into the same sums: hi and mid, then 2^-30 p
+// and lo.  The 2^-30 p (far below the rounding of hi's sums) is there because the
+// second pass may leave no zero in a row whose weight is not zero: an infinite
+// value times 0 would turn that row's sum into NaN.  lo in sums of its own took 64
+// registers more with rows of 256, and the kernel spilled as many (four layers, 8
+// sequences of 16k, one KV head: 230 us a step, 165 with the shared sums).
 #include <type_traits>
 
 #include "kernels.h"
@@ -365,9 +371,9 @@ struct Row {
 };
 
 // Rows of P: query head h of part p sits in row p * G + h.  With G = 8 the
-// sixteen rows hold two parts, the third is accumulated apart.
+// sixteen rows hold two parts at a time: two passes.
 template <bool BF16, int G>
-constexpr int parts_apart() { return BF16 && G == 8 ? 1 : 0; }
+constexpr bool two_passes() { return BF16 && G == 8; }
 
 // A maximum as the reference of exponents: 2^(x - reference(M)) is 0 for x = -inf,
 // also where no score above -inf came yet.  States without such a score are folded
@@ -426,8 +432,8 @@ __device__ __forceinline__ float column_max(float v) {
 // c16 of block k; the parts of a bf16 weight are added here.  Where a value row
 // holds an infinity, the leading part has the result and the others may hold
 // 0 * inf, so those count only while they are finite.
-template <bool BF16, int D, int G, typename Acc, typename Acc2>
-__device__ __forceinline__ void store_state(const Acc& acc, const Acc2& acc2, float* st, int lane) {
+template <bool BF16, int D, int G, typename Acc>
+__device__ __forceinline__ void store_state(const Acc& acc, float* st, int lane) {
     constexpr int S = D + 4;
     const int c16 = lane & 15, q4 = lane >> 4;
 #pragma unroll
@@ -457,8 +463,7 @@ __device__ __forceinline__ void store_state(const Acc& acc, const Acc2& acc2, fl
             for (int i = 0; i < 4; i += 2) {
                 const float x0 = q4 < 2 ? v[i] : finite_or_0(v[i]);
                 const float x1 = q4 < 2 ? v[i + 1] : finite_or_0(v[i + 1]);
-                const float lo = finite_or_0(q4 < 2 ? acc2[k][i] : acc2[k][i + 1]);
-                col[(h + i) * S] = add_halves(x0, x1) + lo;
+                col[(h + i) * S] = add_halves(x0, x1);
             }
         }
     }
@@ -478,7 +483,7 @@ attention_kernel(AttnArgs a) {
     constexpr int NL = R::kLoads;
     constexpr int NQ = R::kQRegs;
     constexpr int NB = D / 16;                    // column blocks of the accumulators
-    constexpr int kApart = parts_apart<BF16, G>();
+    constexpr bool kTwice = two_passes<BF16, G>();
     static_assert(G * (D + 4) * 4 <= R::kTileLds, "wave state fits its tile");
     static_assert(64 * 24 <= R::kTileLds, "a wave's folded states fit its tile");
 
@@ -508,7 +513,7 @@ attention_kernel(AttnArgs a) {
     float* rel_kept = reinterpret_cast<float*>(kt + R::kTileLds);  // [tile][wide][kTile]
     // which 8 bits of p the lane's rows of P carry: leading (0), middle (1), trailing (2 and up)
     const uint32_t mask1 = c16 / G >= 1 ? 0xFFFF0000u : 0u;
-    const uint32_t mask2 = !kApart && c16 / G >= 2 ? 0xFFFF0000u : 0u;
+    const uint32_t mask2 = c16 / G >= 2 ? 0xFFFF0000u : 0u;
     const bool rel_abs = a.rel_mode == 0;
 
     const Plan plan = make_plan(PlanInput{a.n_active, a.B, a.Hkv, hw, a.grid}, kTile, plan_lds);
@@ -627,12 +632,9 @@ attention_kernel(AttnArgs a) {
         load_tile(rv, off, vx);
 
         float m = -INFINITY, l = 0.f;             // of the lane's column (l: its own tokens)
-        floatx4 acc[NB], acc2[kApart ? NB : 1];
+        floatx4 acc[NB];
 #pragma unroll
-        for (int k = 0; k < NB; ++k) {
-            acc[k] = floatx4{0.f, 0.f, 0.f, 0.f};
-            if constexpr (kApart) acc2[k] = floatx4{0.f, 0.f, 0.f, 0.f};
-        }
+        for (int k = 0; k < NB; ++k) acc[k] = floatx4{0.f, 0.f, 0.f, 0.f};
 
         int c0 = t0;                              // first tile of the chunk
         for (;;) {
@@ -739,10 +741,7 @@ attention_kernel(AttnArgs a) {
 #pragma unroll
                 for (int k = 0; k < NB; ++k)
 #pragma unroll
-                    for (int i = 0; i < 4; ++i) {
-                        acc[k][i] *= row_sc[i];
-                        if constexpr (kApart) acc2[k][i] *= row_sc[i];
-                    }
+                    for (int i = 0; i < 4; ++i) acc[k][i] *= row_sc[i];
             }
             float p[NBLK][4];
             const float mr = reference(m);
@@ -764,18 +763,20 @@ attention_kernel(AttnArgs a) {
 #pragma unroll
                         for (int e = 0; e < 2; ++e) {
                             float f = p[blk][i + e];
-                            f -= __uint_as_float(__float_as_uint(f) & mask1);
-                            f -= __uint_as_float(__float_as_uint(f) & mask2);
-                            u[e] = __float_as_uint(f);
-                            if constexpr (kApart) {
-                                float lo = p[blk][i + e];
-                                lo -= __uint_as_float(__float_as_uint(lo) & 0xFFFF0000u);
-                                lo -= __uint_as_float(__float_as_uint(lo) & 0xFFFF0000u);
-                                u2[e] = __float_as_uint(lo);
+                            if constexpr (kTwice) {
+                                const float hi = __uint_as_float(__float_as_uint(f) & 0xFFFF0000u);
+                                const float rest = f - hi;
+                                const float lo = rest - __uint_as_float(__float_as_uint(rest) & 0xFFFF0000u);
+                                u[e] = __float_as_uint(mask1 ? rest : f);
+                                u2[e] = __float_as_uint(mask1 ? lo : f * 0x1p-30f);
+                            } else {
+                                f -= __uint_as_float(__float_as_uint(f) & mask1);
+                                f -= __uint_as_float(__float_as_uint(f) & mask2);
+                                u[e] = __float_as_uint(f);
                             }
                         }
                         pw[blk * 2 + i / 2] = (int)__builtin_amdgcn_perm(u[1], u[0], 0x07060302u);
-                        if constexpr (kApart) pw2[blk * 2 + i / 2] = (int)__builtin_amdgcn_perm(u2[1], u2[0], 0x07060302u);
+                        if constexpr (kTwice) pw2[blk * 2 + i / 2] = (int)__builtin_amdgcn_perm(u2[1], u2[0], 0x07060302u);
                     }
                 // V's columns: 4 tokens per transposed read (rows 4 q4 .. 4 q4 + 3 of a block)
                 const char* vb = vt + (q4 * 4 + c16 / 4) * R::kVStride + (c16 % 4) * 8;
@@ -789,9 +790,9 @@ attention_kernel(AttnArgs a) {
                         const shortx4 v = column(0);
                         acc[k] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(
                             __builtin_bit_cast(shortx4, intx2{pw[0], pw[1]}), v, acc[k], 0, 0, 0);
-                        if constexpr (kApart)
-                            acc2[k] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(
-                                __builtin_bit_cast(shortx4, intx2{pw2[0], pw2[1]}), v, acc2[k], 0, 0, 0);
+                        if constexpr (kTwice)
+                            acc[k] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(
+                                __builtin_bit_cast(shortx4, intx2{pw2[0], pw2[1]}), v, acc[k], 0, 0, 0);
                     } else {
 #pragma unroll
                         for (int j = 0; j < NBLK; j += 2) {
@@ -800,10 +801,10 @@ attention_kernel(AttnArgs a) {
                             const int* w = pw + 2 * j;
                             acc[k] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
                                 __builtin_bit_cast(bf16x8, intx4{w[0], w[1], w[2], w[3]}), v, acc[k], 0, 0, 0);
-                            if constexpr (kApart) {
+                            if constexpr (kTwice) {
                                 const int* w2 = pw2 + 2 * j;
-                                acc2[k] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
-                                    __builtin_bit_cast(bf16x8, intx4{w2[0], w2[1], w2[2], w2[3]}), v, acc2[k], 0, 0, 0);
+                                acc[k] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+                                    __builtin_bit_cast(bf16x8, intx4{w2[0], w2[1], w2[2], w2[3]}), v, acc[k], 0, 0, 0);
                             }
                         }
                     }
@@ -845,7 +846,7 @@ attention_kernel(AttnArgs a) {
             ml_lds[(wave * 2) * G + lane] = m;
             ml_lds[(wave * 2 + 1) * G + lane] = l;
         }
-        store_state<BF16, D, G>(acc, acc2, reinterpret_cast<float*>(kt), lane);
+        store_state<BF16, D, G>(acc, reinterpret_cast<float*>(kt), lane);
         lds_barrier();
         const int heads = hw * G;                 // query heads of the piece
         const size_t slot0 = (size_t)(slot - part) * heads;        // the pair's first partial

@@ -131,7 +131,7 @@ def test_relevance_beyond_the_room(gpu, batch, n):
         A.asrkf_destroy(ctx)
 
 
-@pytest.mark.parametrize("layout", ["bf16-128-g4", "bf16-128-g8", "bf16-64-g2", "bf16-64-g1", "f32-64-g4"])
+@pytest.mark.parametrize("layout", ["bf16-128-g4", "bf16-128-g8", "bf16-64-g2", "bf16-64-g1", "bf16-256-g8", "f32-64-g4"])
 def test_infinite_values(gpu, layout):
     """An infinity in a value row reaches the dims it sits in, with its sign, and
     no others; two of opposite sign give NaN there."""
@@ -286,5 +286,32 @@ def test_values_near_the_largest(gpu, layout):
         w = torch.softmax(K[:, 0, 0].double() / math.sqrt(D), 0)
         ref = torch.einsum("n,nhd->hd", w, V.double()).repeat_interleave(Hq // Hkv, 0)
         assert float(((out.double() - ref) / ref.abs().clamp_min(1.0)).abs().max()) <= 1e-5
+    finally:
+        A.asrkf_destroy(ctx)
+
+
+@pytest.mark.parametrize("n", [1, 33, 700, 9000])
+@pytest.mark.parametrize("layout", ["bf16-64-g8", "bf16-128-g8", "bf16-256-g8"])
+def test_eight_query_heads_error(gpu, layout, n):
+    """Eight query heads take their weights' 24 bits in two passes.  Bound in the 2-norm: weights exact to fp32 and sums in fp32
+    give about 2e-7 (measured 1.0e-7 to 1.7e-7); a weight cut to 16 bits would give
+    some 1e-5 / sqrt(n), 1e-6 and more up to 100 tokens."""
+    torch = gpu
+    import paper_2512_11221_amd as A
+    Hq, Hkv, D = {"bf16-64-g8": (16, 2, 64), "bf16-128-g8": (16, 2, 128), "bf16-256-g8": (8, 1, 256)}[layout]
+    g = torch.Generator(device="cuda").manual_seed(31 + n)
+    K, V = (torch.randn((n + 1, Hkv, D), generator=g, device="cuda", dtype=torch.bfloat16) for _ in range(2))
+    q = torch.randn((1, Hq, D), generator=g, device="cuda", dtype=torch.bfloat16)
+    out = torch.empty((1, Hq, D), device="cuda")
+    ctx = A.asrkf_init(A.make_config(1, 1, Hq, Hkv, D, n + 2, 16, 0.0, 2.0, 16, dtype="bf16"))
+    try:
+        A.asrkf_prefill(ctx, 0, 0, K, V, n)
+        A.asrkf_decode_step(ctx, 0, q, K[n:].contiguous(), V[n:].contiguous(), out)
+        x = torch.matmul(q[0].double().view(Hkv, 8, D), K.double().permute(1, 2, 0).contiguous())
+        p = torch.softmax(x / math.sqrt(D), -1)
+        ref = torch.matmul(p, V.double().permute(1, 0, 2).contiguous()).view(Hq, D)
+        err = float((out[0].double() - ref).norm() / ref.norm())
+        print(f"{layout} n {n}: {err:.2e}")
+        assert err <= 4e-7
     finally:
         A.asrkf_destroy(ctx)
