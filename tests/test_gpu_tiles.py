@@ -315,3 +315,38 @@ def test_eight_query_heads_error(gpu, layout, n):
         assert err <= 4e-7
     finally:
         A.asrkf_destroy(ctx)
+
+
+@pytest.mark.parametrize("layout,batch", [
+    ("bf16-64-g1", 8), ("bf16-64-g1", 16), ("bf16-64-g1", 32), ("bf16-64-g1", 64), ("bf16-64-g1", 70),
+    ("bf16-128-g4", 40), ("bf16-128-g4", 100), ("bf16-128-g4", 300), ("bf16-128-g8", 200), ("bf16-256-g2", 90),
+    ("f32-128-g1", 100), ("f32-64-g8", 300)])
+def test_pairs_shared_by_workgroups_of_several_heads(gpu, layout, batch):
+    """Ragged batches whose pairs are cut by the ranges of workgroups that take one,
+    two, four or eight KV heads together: every sequence's outputs against 64 bits."""
+    torch = gpu
+    import paper_2512_11221_amd as A
+    lay = LAYOUTS[layout]
+    Hq, Hkv, D = lay["n_q_heads"], lay["n_kv_heads"], lay["head_dim"]
+    dt = torch.bfloat16 if lay["dtype"] == "bf16" else torch.float32
+    g = torch.Generator(device="cuda").manual_seed(37)
+    lens = [1 + (97 * b * b + 31 * b) % 700 for b in range(batch)]
+    n = max(lens)
+    K, V = (torch.randn((n + 1, Hkv, D), generator=g, device="cuda", dtype=dt) for _ in range(2))
+    q = torch.randn((batch, Hq, D), generator=g, device="cuda", dtype=dt)
+    new = [x[n:].expand(batch, Hkv, D).contiguous() for x in (K, V)]
+    out = torch.empty((batch, Hq, D), device="cuda")
+    ctx = A.asrkf_init(A.make_config(1, batch, Hq, Hkv, D, n + 2, 16, 0.0, 2.0, 16, dtype=lay["dtype"]))
+    try:
+        for b in range(batch):
+            A.asrkf_prefill(ctx, 0, b, K, V, lens[b])
+        A.asrkf_decode_step(ctx, 0, q, new[0], new[1], out)
+        Kd, Vd = (x.double().permute(1, 0, 2).contiguous() for x in (K, V))       # [Hkv][n + 1][D]
+        x = torch.matmul(q.double().view(batch, Hkv, Hq // Hkv, D), Kd.transpose(1, 2).contiguous())
+        pos = torch.arange(n + 1, device="cuda")
+        off = (pos >= torch.tensor(lens, device="cuda")[:, None]) & (pos < n)     # the new token is row n
+        p = torch.softmax((x / math.sqrt(D)).masked_fill(off[:, None, None], -math.inf), -1)
+        ref = torch.matmul(p, Vd).view(batch, Hq, D)
+        assert float((out.double() - ref).abs().max()) <= OUT_TOL * 1.5           # |v| < 5.2
+    finally:
+        A.asrkf_destroy(ctx)
