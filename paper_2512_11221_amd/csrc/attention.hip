@@ -852,8 +852,9 @@ attention_kernel(AttnArgs a) {
         const size_t slot0 = (size_t)(slot - part) * heads;        // the pair's first partial
         const Finish fin{a.out + ((size_t)b * a.Hq + gi * heads) * D,
                          a.norm ? a.norm + ((size_t)b * a.Hq + gi * heads) * 2 : nullptr};
-        // partials: offsets stay far below 2 GiB (32 MiB at the widest layout and batch 1024)
-        const auto rp = buffer(a.part_acc, 0x7FFFFFFF), rm = buffer(a.part_ml, 0x7FFFFFFF);
+        // the partials as allocated: (workgroups x 8 KV heads + pairs) query heads, 40 MiB
+        // at 256 workgroups, the widest token rows and 1024 sequences
+        const auto rp = buffer(a.part_acc, a.part_heads * D * 4), rm = buffer(a.part_ml, a.part_heads * 8);
         // four dims of a head per thread
         for (int e = threadIdx.x * 4; e < heads * D; e += kThreads * 4) {
             const int hh = e / D, d = e % D;
@@ -1074,13 +1075,18 @@ void attention_layout(const int32_t* plen, int batch, int t, int n_kv_heads, int
     // are stored once, at the end.  With more pairs a workgroup would walk several
     // short pieces one after the other, each with its own round trips: the waves take
     // as many heads side by side as bring the pairs down to the workgroups, and no
-    // more (16 x 100 to 900 tokens, 32 heads: 33.1 us a launch with one head, 29.0
-    // with two; 128 x 100 to 500 tokens, 8 heads: 49.0 us with eight, 42.3 with four).
-    // With long pieces the relevance values of every head would be stored among the
-    // row loads, where they cost ten times their bytes: eight heads, whose values are
-    // summed first (64 x 17k tokens: 730 us with one head, 670 with eight).  The
-    // choice rests on the prompts alone, so a step replayed from a graph is dealt like
-    // the same step run eagerly.
+    // more (16 x 100 to 900 tokens, 32 heads: 35.4 us a launch with one head, 31.5
+    // with two; 128 x 100 to 500 tokens, 8 heads: 45.0 us with eight, 43.8 with four,
+    // 54.8 with one).  With long pieces the relevance values of every head would be
+    // stored among the row loads, where they cost ten times their bytes: eight heads,
+    // whose values are summed first (64 x 2k to 32k tokens: 684 us with one head, 662
+    // with eight).  The softmax reading keeps one value per query head either way and
+    // its room holds fewer tiles; the same rule serves it (64 x 2k to 32k tokens: 831
+    // us with one head, 808 with eight; 8 x 65k tokens of eight query heads, just on
+    // this side of the line: 417 and 455).  The choice rests on the prompts alone, so
+    // a step replayed from a graph is dealt like the same step run eagerly; lists that
+    // grow long from short prompts stay with the heads chosen for those (64 sequences
+    // grown from nothing to 18k tokens: 712 us a launch).
     int hw = 1;
     if (tiles * n_kv_heads > (int64_t)room_tiles(tile) * grid) hw = n_kv_heads < 8 ? n_kv_heads : 8;
     while (hw < 8 && hw < n_kv_heads && (int64_t)batch * n_kv_heads / hw > grid) hw *= 2;

@@ -65,6 +65,7 @@ struct AttnArgs {
     int32_t* t_dev;           // first layer of a step: advanced by one (steps started), else null
     float* part_acc;          // [grid + pairs][heads][D] of the pairs that several workgroups share
     float* part_ml;           // [grid + pairs][heads][2]: (max in log2 units, sum)
+    int32_t part_heads;       // query heads that the partials have room for
     int32_t* ticket;          // [B][Hkv] workgroups of a pair that have stored their partial; zero
                               // between launches
     float* out;               // [B][Hq][D]

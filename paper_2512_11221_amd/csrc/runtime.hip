@@ -845,6 +845,7 @@ asrkf_status decode_step_impl(asrkf_ctx* ctx, int32_t layer, const void* q, cons
     a.rel_cap = ctx->rel_cap;
     a.part_acc = ctx->part_acc;
     a.part_ml = ctx->part_ml;
+    a.part_heads = (int32_t)part_heads(ctx);
     a.ticket = ctx->ticket;
     a.out = out;
     a.norm = ctx->norm ? ctx->norm + inst0 * c.n_q_heads * 2 : nullptr;
