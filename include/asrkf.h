@@ -96,8 +96,8 @@ typedef struct {
     int32_t batch;           /* sequences, 1 .. 1024 */
     int32_t n_q_heads;       /* H in Eq. 2 */
     int32_t n_kv_heads;      /* 1, 2, 4, 8, 16 or 32; n_q_heads / n_kv_heads in {1, 2, 4, 8};
-                                with 16 KV heads at most 4 q heads per KV head, with 32 at
-                                most 2, and for fp32 rows of 128 at most 16 KV heads */
+                                at most 64 q heads, and at most 8 KiB of K per token (32 KV
+                                heads of 128 bf16, 16 of 256 bf16 or of 128 fp32) */
     int32_t head_dim;        /* 64, 128 or 256 (256 with bf16 rows only) */
     int32_t max_ctx;         /* positions per sequence: prompt + decode steps */
     int32_t window_K;        /* protected window of most recent positions (Sec. 3.2; paper: 32) */
@@ -202,11 +202,11 @@ asrkf_status asrkf_decode_step(asrkf_ctx* ctx, int32_t layer, const void* q,
  * call (code under HIP graph capture, serving loops, harnesses that forbid
  * hipMalloc).  Same arguments, work and results as asrkf_decode_step (the same
  * kernels); it allocates nothing and creates no event.  Its split-K partials
- * (per partial slot and query head: head_dim + 2 floats; slots = attention
- * grid + batch, where the grid is the number of attention workgroups resident
- * at once, one per compute unit at the LLaMA-3-8B shape) live in a static
- * device array of 32 MiB that the library holds on every GPU it runs on until
- * the process ends; asrkf_init resolves its address on the context's device.
+ * (head_dim + 2 floats per query head, at most (grid + batch) * n_q_heads query
+ * heads, where the grid is the number of attention workgroups resident at
+ * once, one per compute unit) live in a static device array of 32 MiB that
+ * the library holds on every GPU it runs on until the process ends;
+ * asrkf_init resolves its address on the context's device.
  * EINVAL, with nothing done, when the partials of this context exceed 32 MiB
  * ((grid + batch) * n_q_heads * (head_dim + 2) * 4 + 8 * batch bytes).  Every
  * call on one GPU shares the array and leaves its contents behind: calls on

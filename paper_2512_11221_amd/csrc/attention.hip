@@ -48,21 +48,12 @@
 // sequences of 16k, one KV head: 230 us a step, 165 with the shared sums).
 #include <type_traits>
 
+#include "attention_split.h"
 #include "kernels.h"
 
 namespace asrkf {
 namespace {
 
-// What a piece costs a workgroup beside its rows (set-up round trips, merge,
-// partial), in tiles of one KV head streamed: about 6 us against 0.6 us a tile.
-constexpr int kPieceCost = 10;
-// Fewest tiles of one KV head worth a workgroup, and the share up to which only
-// half of the workgroups are used: with little work the launch is bound by fixed
-// latencies, and 256 workgroups start two microseconds later than 128 (one
-// sequence of 4093 tokens, 8 KV heads: 14.4 us with 128 workgroups of 8 tiles,
-// 15.4 with 256 of 4; of 1500 tokens: 11.9 with 96 of 4, 13.2 with 48 of 8).
-constexpr int kMinTiles = 4;
-constexpr int kHalfTiles = 8;
 // raw buffer descriptor word 3 for gfx9-class targets (32-bit data, no swizzle)
 constexpr int kBufferFlags = 0x00020000;
 // cache policy of the K/V row loads: non-temporal.  Each row is read once per
@@ -127,55 +118,15 @@ __device__ __forceinline__ void lds_barrier() {
 
 // ---- the split ----
 //
-// Tiles of the (sequence, head group) pairs dealt to the workgroups, from the
-// active counts.  Two forms, chosen by what the longest share would be:
-//  aligned   every pair is cut into parts of at most `share` tiles, one
-//            workgroup each (a workgroup never takes a second piece, which
-//            would cost it set-up, merge and partial again);
-//  straddled the pairs' tile lists, each preceded by `cost` virtual tiles, are
-//            concatenated and cut into equal ranges: when the lengths differ so
-//            much, or the pairs are so many, that aligned parts would leave some
-//            workgroup more than a piece's cost above the average.
-// Batches of up to 64 sequences are planned by every wave for itself, one
-// sequence per lane, without a barrier; larger ones by wave 0 into LDS.
-struct Plan {
-    int tile;                       // tokens per tile
-    int groups, cost, limit;        // head groups per sequence, piece cost in tiles, workgroups
-    bool aligned;
-    int share;                      // aligned: tiles per part; straddled: tiles per range (the first
-    int extra;                      //   `extra` ranges have one more)
-    int live;                       // workgroups with work
-    // sequence b owns units [off, off + units): workgroups (aligned) or tiles (straddled)
+// The split with the lists it deals.  Batches of up to 64 sequences are planned by
+// every wave for itself, one sequence per lane, without a barrier; larger ones by
+// wave 0 into LDS.
+struct Plan : Split {
+    // sequence b owns units [off, off + units)
     int n, units, off;              // of the lane's sequence (up to 64 sequences)
     const int32_t* lds;             // [B + 1] offsets, then [B] counts (more than 64)
     int B;
 
-    __device__ __forceinline__ int parts(int tiles) const { return (tiles + share - 1) / share; }
-    __device__ __forceinline__ int tiles_of(int n) const { return (n + tile - 1) / tile; }
-    __device__ __forceinline__ int units_of(int n) const {
-        const int tiles = tiles_of(n);
-        return n == 0 ? 0 : groups * (aligned ? parts(tiles) : tiles + cost);
-    }
-    // total: tiles of all sequences, longest: of the longest, filled: sequences with any
-    __device__ __forceinline__ void choose(int total, int longest, int filled) {
-        const int average = (total * groups + limit - 1) / limit;
-        const int most = limit / max(1, filled * groups);         // parts a pair can have
-        share = max(kMinTiles / min(kMinTiles, limit_heads), most > 0 ? (longest + most - 1) / most : 0);
-        share = max(share, min(kHalfTiles / min(kHalfTiles, limit_heads), 2 * average));
-        aligned = most > 0 && share <= max(average + cost, kHalfTiles);
-    }
-    int limit_heads;                // KV heads a workgroup takes together
-    __device__ __forceinline__ void ranges(int T) {               // straddled, after the scan
-        live = max(1, min(limit, T / kMinTiles));
-        share = T / live;
-        extra = T - share * live;
-        if (T == 0) live = 0;
-    }
-    __device__ __forceinline__ int start(int w) const { return w * share + min(w, extra); }
-    __device__ __forceinline__ int owner(int x) const {           // the range holding tile x
-        const int head = extra * (share + 1);
-        return x < head ? x / (share + 1) : extra + (x - head) / share;
-    }
     // the sequence that owns unit x
     __device__ __forceinline__ int find(int x) const {
         if (B <= 64) return __popcll(__ballot((int)(threadIdx.x & 63) < B && off + units <= x));
@@ -187,16 +138,6 @@ struct Plan {
         while (wave_uniform(lds[l0 + 1]) <= x) ++l0;              // past empty lists
         return l0;
     }
-    __device__ __forceinline__ void range(int w, int& x, int& x_end) const {
-        x = aligned ? w : start(w);
-        x_end = aligned ? w + 1 : start(w + 1);
-    }
-    // The workgroup of index i takes range w: workgroups are dealt to the 8 XCDs
-    // round robin, and when every workgroup has work each XCD takes a contiguous
-    // block of ranges.  Any one-to-one map gives the same partials.
-    __device__ __forceinline__ int range_of(int i) const {
-        return live == limit && limit % 8 == 0 ? (i % 8) * (limit / 8) + i / 8 : i;
-    }
     __device__ __forceinline__ int offset(int b) const {
         return B <= 64 ? __builtin_amdgcn_readlane(off, b) : wave_uniform(lds[b]);
     }
@@ -205,50 +146,6 @@ struct Plan {
     }
 };
 
-// One workgroup's part of a pair.
-struct Piece {
-    int b, n;                       // sequence, its active count
-    int group;                      // head group
-    int t0, t1;                     // tiles
-    int n_parts, part, slot;        // workgroups sharing the pair, which of them, partial slot
-};
-
-// The next piece of range w from unit x on (x moves past it); false: only
-// virtual tiles were left.
-__device__ __forceinline__ bool next_piece(const Plan& plan, int w, int& x, int x_end, Piece& p) {
-    while (x < x_end) {
-        p.b = plan.find(x);
-        const int so = plan.offset(p.b);
-        p.n = plan.count(p.b);
-        const int tiles = plan.tiles_of(p.n);
-        if (plan.aligned) {
-            p.n_parts = plan.parts(tiles);
-            p.group = (x - so) / p.n_parts;
-            p.part = x - so - p.group * p.n_parts;
-            p.t0 = p.part * plan.share;
-            p.t1 = min(tiles, p.t0 + plan.share);
-            p.slot = x;
-            ++x;
-            return true;
-        }
-        const int units = tiles + plan.cost;      // of one head group
-        p.group = (x - so) / units;
-        const int first = so + p.group * units + plan.cost;       // the pair's first tile
-        const int end = min(first + tiles, x_end);
-        const int from = max(x, first);
-        x = end;
-        if (end <= first) continue;               // virtual tiles only
-        p.t0 = from - first;
-        p.t1 = end - first;
-        const int w0 = plan.owner(first);
-        p.n_parts = plan.owner(first + tiles - 1) - w0 + 1;
-        p.part = w - w0;
-        p.slot = w + p.b * plan.groups + p.group;
-        return true;
-    }
-    return false;
-}
-
 struct PlanInput {
     const int32_t* n_active;
     int B, Hkv, heads_per_group, grid;
@@ -256,11 +153,7 @@ struct PlanInput {
 
 __device__ __forceinline__ Plan make_plan(const PlanInput& a, int tile, int32_t* lds) {
     Plan p;
-    p.tile = tile;
-    p.groups = a.Hkv / a.heads_per_group;
-    p.cost = max(1, kPieceCost / a.heads_per_group);
-    p.limit = a.grid;
-    p.limit_heads = a.heads_per_group;
+    p.init(tile, a.Hkv, a.heads_per_group, a.grid);
     p.B = a.B;
     p.lds = lds;
     const int lane = threadIdx.x & 63;
@@ -339,9 +232,7 @@ __device__ __forceinline__ Plan make_plan(const PlanInput& a, int tile, int32_t*
         p.aligned = wave_uniform(summary[1]) != 0;
         total = wave_uniform(off[a.B]);
     }
-    p.extra = 0;
-    if (p.aligned) p.live = total;
-    else p.ranges(total);
+    p.ranges(total);
     return p;
 }
 
@@ -353,7 +244,7 @@ struct Row {
     static constexpr int kBytes = D * kElem;              // one token, one KV head
     static constexpr int kLanes = kBytes / 16;            // lanes per row in a load
     // tokens per tile: 16 KB of K and V rows, in a wave's registers while they travel
-    static constexpr int kTile = 8192 / kBytes;
+    static constexpr int kTile = tile_tokens(kBytes);
     static constexpr int kBlocks = kTile / 16;            // score blocks of 16 tokens
     static constexpr int kLoads = kTile * kLanes / 64;    // load instructions per tile (K or V)
     // LDS row strides: the padding shifts consecutive rows by 4 (K) and 8 (V)
@@ -364,9 +255,9 @@ struct Row {
     static constexpr int kVStride = kBytes + 32;
     static constexpr int kTileLds = kTile * kVStride;
     // room for the relevance values a wave keeps before they are stored
-    static constexpr int kRelLds = 8192;
+    static constexpr int kRelLds = kRelRoomBytes;
     static constexpr int kWaveLds = kTileLds + kRelLds;
-    static constexpr int kWaves = 8;
+    static constexpr int kWaves = kAttnWaves;
     static constexpr int kQRegs = BF16 ? D / 32 : D / 16; // 16-byte pieces of q per lane
 };
 
@@ -524,7 +415,7 @@ attention_kernel(AttnArgs a) {
     x = wave_uniform(x);
     x_end = wave_uniform(x_end);
     Piece pc;
-    while (next_piece(plan, w, x, x_end, pc)) {
+    while (next_piece(plan, plan, w, x, x_end, pc)) {
         constexpr int kPer = 64 / R::kLanes;
         const int entry = R::kLanes == 8 ? (lane & 7) * 8 + (lane >> 4) * 2 + ((lane >> 3) & 1)
                                          : (lane % NL) * kPer + lrow;
@@ -1036,18 +927,12 @@ hipError_t dispatch(const AttnArgs& a, int dtype_bf16, int head_dim, int group, 
 }  // namespace
 
 // The head layouts of the interface: token rows (every KV head) of at most
-// 8 KiB, at most 32 blocks of four query heads (two with rows of 256) per
-// token, and at most 8 / (blocks / 8) heads a block.
+// 8 KiB and at most 64 query heads.
 bool attention_shape_supported(int dtype_bf16, int head_dim, int group, int n_kv_heads) {
     if (head_dim != 64 && head_dim != 128 && head_dim != 256) return false;
     if (head_dim == 256 && !dtype_bf16) return false;
     if (group != 1 && group != 2 && group != 4 && group != 8) return false;
-    const int most = head_dim / 8 >= 32 ? 2 : 4;
-    const int parts = group > most ? group / most : 1;
-    const int blocks = n_kv_heads * parts;
-    const int per_token = blocks > 8 ? blocks / 8 : 1;
-    return n_kv_heads * head_dim * (dtype_bf16 ? 2 : 4) <= 8192 && per_token <= 4 &&
-           group / parts <= 8 / per_token;
+    return n_kv_heads * head_dim * (dtype_bf16 ? 2 : 4) <= 8192 && group * n_kv_heads <= 64;
 }
 
 hipError_t launch_attention(const AttnArgs& a, int dtype_bf16, int head_dim, int group,
@@ -1058,46 +943,6 @@ hipError_t launch_attention(const AttnArgs& a, int dtype_bf16, int head_dim, int
 hipError_t attention_occupancy(const AttnArgs& a, int dtype_bf16, int head_dim, int group,
                                int* blocks_per_cu) {
     return dispatch(a, dtype_bf16, head_dim, group, Launch{0, nullptr, nullptr, nullptr, blocks_per_cu});
-}
-
-namespace {
-// tiles whose relevance values a workgroup has room for
-constexpr int room_tiles(int tile) { return 8192 / (tile * 4) * 8; }
-}  // namespace
-
-void attention_layout(const int32_t* plen, int batch, int t, int n_kv_heads, int row_bytes, int grid,
-                      int* heads_per_group, int* launch) {
-    const int tile = 8192 / row_bytes;
-    int64_t tiles = 0;
-    for (int b = 0; b < batch; ++b) tiles += (plen[b] + tile) / tile;
-    // One KV head per piece while every pair can have a workgroup and the pieces are
-    // short: a pair's partials and its merge are smallest, and its relevance values
-    // are stored once, at the end.  With more pairs a workgroup would walk several
-    // short pieces one after the other, each with its own round trips: the waves take
-    // as many heads side by side as bring the pairs down to the workgroups, and no
-    // more (16 x 100 to 900 tokens, 32 heads: 35.4 us a launch with one head, 31.5
-    // with two; 128 x 100 to 500 tokens, 8 heads: 45.0 us with eight, 43.8 with four,
-    // 54.8 with one).  With long pieces the relevance values of every head would be
-    // stored among the row loads, where they cost ten times their bytes: eight heads,
-    // whose values are summed first (64 x 2k to 32k tokens: 684 us with one head, 662
-    // with eight).  The softmax reading keeps one value per query head either way and
-    // its room holds fewer tiles; the same rule serves it (64 x 2k to 32k tokens: 831
-    // us with one head, 808 with eight; 8 x 65k tokens of eight query heads, just on
-    // this side of the line: 417 and 455).  The choice rests on the prompts alone, so
-    // a step replayed from a graph is dealt like the same step run eagerly; lists that
-    // grow long from short prompts stay with the heads chosen for those (64 sequences
-    // grown from nothing to 18k tokens: 712 us a launch).
-    int hw = 1;
-    if (tiles * n_kv_heads > (int64_t)room_tiles(tile) * grid) hw = n_kv_heads < 8 ? n_kv_heads : 8;
-    while (hw < 8 && hw < n_kv_heads && (int64_t)batch * n_kv_heads / hw > grid) hw *= 2;
-    const int64_t groups = n_kv_heads / hw;
-    const int cost = kPieceCost / hw > 1 ? kPieceCost / hw : 1;
-    const int least = kMinTiles / (hw < kMinTiles ? hw : kMinTiles);
-    int64_t live = 0;
-    for (int b = 0; b < batch && live < grid; ++b)
-        live += groups * (((plen[b] + t + tile - 1) / tile + cost + least - 1) / least);
-    *heads_per_group = hw;
-    *launch = live < grid ? (live > 1 ? (int)live : 1) : grid;
 }
 
 }  // namespace asrkf

@@ -7,12 +7,10 @@
 
 namespace asrkf {
 
-// Split-K attention.  The active list of every (sequence, KV head) pair, cut
-// into tiles, concatenated, is cut into one equal contiguous range per
-// workgroup of a fixed grid (derived on the device from the active counts, no
-// host round trip).  A pair that several workgroups share leaves one partial
-// (m, l, acc) per workgroup, at slot (workgroup + pair); the last to arrive
-// folds them.
+// Split-K attention: the tiles of every (sequence, KV head group) pair are dealt
+// to the workgroups of a fixed grid, from the active counts on the device
+// (attention_split.h).  A pair that several workgroups share leaves one partial
+// (m, l, acc) per workgroup, at consecutive slots; the last to arrive folds them.
 constexpr int kMaxBatch = 1024;
 
 // A low-relevance detection of the token at state index o in step t: the new
@@ -231,11 +229,6 @@ hipError_t launch_attention(const AttnArgs& a, int dtype_bf16, int head_dim, int
                             int grid, hipStream_t s, hipEvent_t start, hipEvent_t stop);
 hipError_t attention_occupancy(const AttnArgs& a, int dtype_bf16, int head_dim, int group,
                                int* blocks_per_cu);
-// How a step's attention is laid out when sequence b lists up to plen[b] + t
-// positions: KV heads a workgroup takes together, and how many workgroups to
-// launch (at least those with work, at most grid: idle ones delay the others).
-void attention_layout(const int32_t* plen, int batch, int t, int n_kv_heads, int row_bytes, int grid,
-                      int* heads_per_group, int* launch);
 hipError_t launch_clear(const ClearArgs& a, hipStream_t s);
 hipError_t launch_compact(const CompactArgs& a, int n_instances, hipStream_t s);
 // Segments per instance (and their length) for the rebuild; 1 = one workgroup per instance.

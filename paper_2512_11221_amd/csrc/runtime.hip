@@ -33,6 +33,7 @@
 #include <rocprofiler-sdk-roctx/roctx.h>
 
 #include "../../include/asrkf.h"
+#include "attention_split.h"
 #include "kernels.h"
 
 using namespace asrkf;
