@@ -279,6 +279,18 @@ __device__ __forceinline__ void fold(float& L, floatx4& o, float wgt, float l, f
     for (int i = 0; i < 4; ++i) o[i] = fmaf(wgt, v[i], o[i]);
 }
 
+// Groups of threads that fold a pair's parts, each spanning the outputs of HEADS
+// KV heads (four values a thread), and the round trips that the fold takes.
+template <int G, int D, int HEADS>
+struct Fold {
+    static constexpr int kThreads = 64 * kAttnWaves;
+    static constexpr int kSpan = HEADS * G * D / 4 < kThreads ? HEADS * G * D / 4 : kThreads;
+    static constexpr int kSlotGroups = kThreads / kSpan < 16 ? kThreads / kSpan : 16;
+    __device__ static __forceinline__ int trips(int heads, int n_parts, int pass) {
+        return (heads * D + kSpan * 4 - 1) / (kSpan * 4) * ((n_parts + kSlotGroups * pass - 1) / (kSlotGroups * pass));
+    }
+};
+
 // Where a piece's outputs go.
 struct Finish {
     float* out;                     // first query head of the piece
@@ -795,14 +807,13 @@ attention_kernel(AttnArgs a) {
                 // kSlotGroups-th slot, all loads of a pass in flight, and the groups'
                 // states are folded in order: one or two round trips for the 16 to
                 // 32 parts of a lone sequence.  A group spans one KV head's outputs, or
-                // eight heads' when a workgroup takes several (few parts, many outputs):
-                // with one head's, the eight in turn took a round trip each (70 sequences
-                // of 600 tokens, 32 heads of 64: 76.6 us a launch, 67.5 now).
-                auto fold_parts = [&](auto WIDE) __attribute__((always_inline)) {
-                constexpr int kSpan = decltype(WIDE)::value * G * D / 4;
-                constexpr int kFoldThreads = kSpan < kThreads ? kSpan : kThreads;
-                constexpr int kSlotGroups = kThreads / kFoldThreads < 16 ? kThreads / kFoldThreads : 16;
+                // eight heads' where that takes fewer round trips (several heads, few
+                // parts): with one head's, eight heads in turn took a round trip each (70
+                // sequences of 600 tokens, 32 heads of 64: 76.6 us a launch, 67.5 now).
                 constexpr int kPass = 4;
+                auto fold_parts = [&](auto WIDE) __attribute__((always_inline)) {
+                using F = Fold<G, D, decltype(WIDE)::value>;
+                constexpr int kFoldThreads = F::kSpan, kSlotGroups = F::kSlotGroups;
                 const int grp = threadIdx.x / kFoldThreads;
                 // a thread's state, in its wave's tile (the relevance values are still kept)
                 auto fold_o = [&](int th) { return reinterpret_cast<floatx4*>(tiles + th / 64 * R::kWaveLds) + th % 64; };
@@ -861,8 +872,10 @@ attention_kernel(AttnArgs a) {
                     if (grp == 0 && mine < heads * D) fin.template write<D>(hh, d, M, L, o);
                 }
                 };
-                if (hw == 1) fold_parts(std::integral_constant<int, 1>{});
-                else fold_parts(std::integral_constant<int, 8>{});
+                if (Fold<G, D, 1>::trips(heads, n_parts, kPass) <= Fold<G, D, 8>::trips(heads, n_parts, kPass))
+                    fold_parts(std::integral_constant<int, 1>{});
+                else
+                    fold_parts(std::integral_constant<int, 8>{});
                 if (threadIdx.x == 0) a.ticket[pair] = 0;      // ready for the next launch
             }
         }
