@@ -81,9 +81,8 @@ def _capture(torch, A, ctx, w, buf):
     return g
 
 
-# two layers; four layers with some 10k tokens per layer, where the
-# first-tile records are built inside the captured restore and used by the
-# captured attention launches
+# two layers; four layers with some 10k tokens per layer, where most workgroups
+# have work and the replayed launches deal each step's lists anew
 _REPLAYED = [dict(), dict(name="graph-hh-records", n_layers=4, batch=4, prefill=[2600, 2400, 2800, 2300],
                           f_hh=[0.35, 0.25, 0.3, 0.2], steps=20)]
 

@@ -350,3 +350,39 @@ def test_pairs_shared_by_workgroups_of_several_heads(gpu, layout, batch):
         assert float((out.double() - ref).abs().max()) <= OUT_TOL * 1.5           # |v| < 5.2
     finally:
         A.asrkf_destroy(ctx)
+
+
+@pytest.mark.parametrize("batch,n", [(66, 1200), (40, 900)])
+def test_logits_of_several_heads_beyond_the_room(gpu, batch, n):
+    """Softmax reading with four and two KV heads of eight query heads together: the
+    room for kept logits is full after eight and sixteen tiles of 64 tokens, so a
+    piece stores them in several chunks.  Which tokens freeze against scores in 64
+    bits, without those within 1e-3 of tau (a weight carries about 1e-5 of
+    relative rounding)."""
+    torch = gpu
+    import paper_2512_11221_amd as A
+    Hq, Hkv, D = 64, 8, 64
+    g = torch.Generator(device="cuda").manual_seed(41)
+    tau = 1.0 / (n + 1)
+    K = torch.randn((batch, n + 1, Hkv, D), generator=g, device="cuda", dtype=torch.bfloat16)
+    q = torch.randn((batch, Hq, D), generator=g, device="cuda", dtype=torch.bfloat16)
+    new = K[:, n].contiguous()
+    out = torch.empty((batch, Hq, D), device="cuda")
+    ctx = A.asrkf_init(A.make_config(1, batch, Hq, Hkv, D, n + 2, 16, tau, 0.25, 16, dtype="bf16",
+                                     relevance="softmax"))
+    try:
+        for b in range(batch):
+            A.asrkf_prefill(ctx, 0, b, K[b], K[b], n)
+        A.asrkf_decode_step(ctx, 0, q, new, new, out)
+        A.asrkf_restore(ctx, None, A.NONE)
+        x = torch.matmul(K.double().permute(0, 2, 1, 3),                          # [B][Hkv][n + 1][G]
+                         q.double().view(batch, Hkv, Hq // Hkv, D).transpose(2, 3).contiguous())
+        s = (torch.softmax(x / math.sqrt(D), 2).sum((1, 3)) / Hq).cpu().numpy()
+        for b in range(batch):
+            st = A.asrkf_get_state(ctx, 0, b, n + 2)
+            want = (s[b] < tau) & (np.arange(n + 1) < n + 1 - 16)
+            clear = np.abs(s[b] - tau) > 1e-3 * tau
+            np.testing.assert_array_equal(st["frozen"][clear], want[clear])
+            assert 0.2 < want.mean() < 0.8
+    finally:
+        A.asrkf_destroy(ctx)
