@@ -527,14 +527,14 @@ asrkf_status asrkf_init(const asrkf_config* cfg, asrkf_ctx** out) {
     // Relevance planes.  A list names distinct device rows, so a plane has room for
     // pool_rows entries.  The planes of as many layers are kept as take a 32nd of the
     // cache (every layer's under Eq. 2, at most a 64th of it, and under the softmax
-    // reading with rows of 128 and four query heads per KV head), or 64 MiB; the
-    // verdicts of every rel_layers layers take a launch of their own, 5 to 8 us (eight
-    // layers of 8 x 8k with eight query heads over rows of 64: 203 us a step with one
-    // launch, 228 with four).  Where that does not fit into the device's memory, one
-    // layer's do.
+    // reading with rows of 128 and four query heads per KV head), or 256 MiB, less than
+    // a thousandth of the device's memory; the verdicts of every rel_layers layers take
+    // a launch of their own, 8 to 16 us (eight layers of 8 x 4k, 64 query heads: 8.67 ms
+    // a request of 32 steps with one launch a step, 9.20 with two).  Where that does
+    // not fit into the device's memory, one layer's do.
     ctx->rel_cap = std::min(ctx->cap, (ctx->pool_rows + 63) / 64 * 64);
     const size_t layer_planes = (size_t)c.batch * ctx->planes * ctx->rel_cap * 4;
-    const size_t kept = std::max(2 * pool_bytes / 32, (size_t)64 << 20) / layer_planes;
+    const size_t kept = std::max(2 * pool_bytes / 32, (size_t)256 << 20) / layer_planes;
     ctx->rel_layers = (int)std::min(std::max(kept, (size_t)1), (size_t)c.n_layers);
     if (ctx->token_scope && c.n_layers > 1) ALLOC(rel_sum, (size_t)c.batch * ctx->rel_cap * 4);
     if (hipMalloc((void**)&ctx->rel, layer_planes * ctx->rel_layers) != hipSuccess) {

@@ -3,7 +3,7 @@ device memory of a context, verdicts of a step in several launches (the planes o
 only some layers are kept), and a context in a device with little memory left.
 
 A plane holds 4 bytes per cached position; a context keeps those of all layers
-up to a 32nd of its K and V rows (or 64 MiB)."""
+up to a 32nd of its K and V rows (or 256 MiB)."""
 import math
 
 import numpy as np
@@ -33,9 +33,9 @@ def _used(torch, A, **kw):
 
 
 @pytest.mark.parametrize("relevance", ["abs", "softmax"])
-@pytest.mark.parametrize("heads", [(32, 8, 128), (32, 4, 64), (8, 1, 64)])
+@pytest.mark.parametrize("heads", [(32, 8, 128), (32, 4, 64), (16, 2, 64)])
 def test_device_memory_of_a_context(gpu, heads, relevance):
-    """K and V rows, a 32nd of them (or 64 MiB) for the planes, 13 bytes of state per position
+    """K and V rows, a 32nd of them (or 256 MiB) for the planes, 13 bytes of state per position
     (unfreeze step, count, flag, list entry), 16 MiB of the rest (split partials,
     small arrays, and what the allocator rounds up)."""
     import paper_2512_11221_amd as A
@@ -44,7 +44,7 @@ def test_device_memory_of_a_context(gpu, heads, relevance):
     rows = 2 * L * B * (n + 1) * Hkv * D * 2
     used = _used(gpu, A, n_layers=L, batch=B, n_q_heads=Hq, n_kv_heads=Hkv, head_dim=D, max_ctx=n,
                  dtype="bf16", relevance=relevance)
-    assert used <= rows + max(rows // 32, 64 << 20) + 13 * L * B * (n + 1) + (16 << 20)
+    assert used <= rows + max(rows // 32, 256 << 20) + 13 * L * B * (n + 1) + (16 << 20)
 
 
 @pytest.mark.parametrize("relevance", ["abs", "softmax"])
@@ -59,9 +59,9 @@ def test_device_memory_with_few_device_rows(gpu, relevance):
     assert used <= pool + (8 << 20) + 39 * L * (n + 1) + 8 * L * rows + (16 << 20)
 
 
-# 20 MiB of planes per layer: three layers' are kept, so eight layers take the
+# 78 MiB of planes per layer: three layers' are kept, so eight layers take the
 # verdicts in launches of three, three and two layers
-L, B, HQ, HKV, D, N = 8, 16, 64, 8, 64, 5000
+L, B, HQ, HKV, D, N = 8, 16, 64, 8, 64, 20000
 
 
 def _inputs(torch):
