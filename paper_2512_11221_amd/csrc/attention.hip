@@ -872,7 +872,7 @@ attention_kernel(AttnArgs a) {
                     if (grp == 0 && mine < heads * D) fin.template write<D>(hh, d, M, L, o);
                 }
                 };
-                if (Fold<G, D, 1>::trips(heads, n_parts, kPass) <= Fold<G, D, 8>::trips(heads, n_parts, kPass))
+                if (hw == 1 || Fold<G, D, 1>::trips(heads, n_parts, kPass) <= Fold<G, D, 8>::trips(heads, n_parts, kPass))
                     fold_parts(std::integral_constant<int, 1>{});
                 else
                     fold_parts(std::integral_constant<int, 8>{});

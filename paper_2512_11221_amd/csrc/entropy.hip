@@ -173,15 +173,16 @@ __device__ void entropy_block(const EntropyArgs& a, int sp, int b) {
 constexpr int kEntries = 4 * kThreads;        // list entries per verdict workgroup
 constexpr int kPlaneGroup = 4;
 
+// CARRY: a token-scope step whose layers are judged by several launches.
+template <bool CARRY>
 __device__ void verdict_block(const VerdictArgs& v, int chunk, int inst) {
     const int n = min(v.n_active[inst], v.rel_cap);      // more only where device rows ran out
     const int i0 = chunk * kEntries + 4 * threadIdx.x;
     if (i0 >= n) return;
     const int b = inst % v.B, state = inst / v.B;
     float s[4] = {0.f, 0.f, 0.f, 0.f};
-    float4* sum = reinterpret_cast<float4*>(v.sum + (size_t)b * v.rel_cap + i0);
-    if (v.add_sum) {
-        const float4 before = *sum;
+    if (CARRY && v.add_sum) {
+        const float4 before = *reinterpret_cast<const float4*>(v.sum + (size_t)b * v.rel_cap + i0);
         s[0] = before.x; s[1] = before.y; s[2] = before.z; s[3] = before.w;
     }
     const int4 pos = *reinterpret_cast<const int4*>(v.list + (size_t)inst * v.cap + i0);
@@ -213,8 +214,8 @@ __device__ void verdict_block(const VerdictArgs& v, int chunk, int inst) {
             }
         }
     }
-    if (v.keep_sum) {
-        *sum = make_float4(s[0], s[1], s[2], s[3]);
+    if (CARRY && v.keep_sum) {
+        *reinterpret_cast<float4*>(v.sum + (size_t)b * v.rel_cap + i0) = make_float4(s[0], s[1], s[2], s[3]);
         return;
     }
     uint8_t* flag = v.flag + (size_t)inst * v.cap;
@@ -225,11 +226,12 @@ __device__ void verdict_block(const VerdictArgs& v, int chunk, int inst) {
             flag[p[k]] = (uint8_t)((s[k] < v.tau_sum ? 1 : 0) | (fabsf(s[k] - v.tau_sum) < v.margin_sum ? 2 : 0));
 }
 
+template <bool CARRY>
 __global__ void __launch_bounds__(kThreads)
 monitor_kernel(EntropyArgs e, VerdictArgs v, int entropy_blocks, int chunks) {
     const int i = blockIdx.x;
     if (i < entropy_blocks) entropy_block(e, i % e.split, i / e.split);
-    else verdict_block(v, (i - entropy_blocks) % chunks, (i - entropy_blocks) / chunks);
+    else verdict_block<CARRY>(v, (i - entropy_blocks) % chunks, (i - entropy_blocks) / chunks);
 }
 
 }  // namespace
@@ -239,7 +241,8 @@ hipError_t launch_monitor(const EntropyArgs* e, const VerdictArgs& v, hipStream_
     const int64_t chunks = (v.rel_cap + kEntries - 1) / kEntries;
     const int64_t blocks = entropy_blocks + chunks * v.states * v.B;
     if (blocks > (1 << 30)) return hipErrorInvalidValue;   // caches of that size exceed any device
-    hipLaunchKernelGGL(monitor_kernel, dim3((unsigned)blocks), dim3(kThreads), 0, s,
+    const auto kernel = v.add_sum || v.keep_sum ? monitor_kernel<true> : monitor_kernel<false>;
+    hipLaunchKernelGGL(kernel, dim3((unsigned)blocks), dim3(kThreads), 0, s,
                        e ? *e : EntropyArgs{}, v, (int)entropy_blocks, (int)chunks);
     return hipGetLastError();
 }
