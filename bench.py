@@ -1,9 +1,8 @@
 """Decode-step throughput of the ASR-KF-EGR hot path on one MI355X.
 
 A step is the whole path for every layer and sequence: append, attention over
-the active cache with relevance and the freeze schedule (one launch per layer)
-plus the split combine, then entropy, recovery and the rebuild of every
-active list.  Inputs are synthetic (seeded generator, device twin) and sit in
+the active cache with relevance (one launch per layer), then entropy and the
+freeze verdicts, recovery and the rebuild of every active list.  Inputs are synthetic (seeded generator, device twin) and sit in
 HBM before the timed region starts.
 
 Prints one JSON line.  value = attended (active) KV token-layers per second,
@@ -131,7 +130,17 @@ def summarize_counters(fetch_dir, write_dir, bench_log, timed, copy_bytes):
 
 
 TRAFFIC_SUMMARY = os.path.join(ROOT, "profiles", "attention_traffic_llama3-8b-32layer.md")
-ATTENTION_SOURCE = os.path.join(ROOT, "paper_2512_11221_amd", "csrc", "attention.hip")
+ATTENTION_SOURCES = [os.path.join(ROOT, "paper_2512_11221_amd", "csrc", f)
+                     for f in ("attention.hip", "attention_split.h")]
+
+
+def attention_sha():
+    import hashlib
+    h = hashlib.sha256()
+    for path in ATTENTION_SOURCES:
+        with open(path, "rb") as f:
+            h.update(f.read())
+    return h.hexdigest()
 
 
 def measured_traffic(workload):
@@ -142,42 +151,56 @@ def measured_traffic(workload):
     algorithmic bytes of the same launches gives a ratio that carries to any
     window of the same workload (the kernel reads 4096 B per attended
     token-layer plus a small fixed part per launch)."""
-    import hashlib
     import re
     if not os.path.exists(TRAFFIC_SUMMARY):
         return None
     text = open(TRAFFIC_SUMMARY).read()
     fields = dict(re.findall(r"^- (\w+): `([^`]*)`", text, flags=re.M))
-    with open(ATTENTION_SOURCE, "rb") as f:
-        sha = hashlib.sha256(f.read()).hexdigest()
-    if fields.get("workload") != workload or fields.get("attention_source_sha256") != sha:
+    if fields.get("workload") != workload or fields.get("attention_source_sha256") != attention_sha():
         return None
     return float(fields["traffic_per_algorithmic_byte"]), fields
+
+
+def heads_together(plen, n_kv_heads, row_bytes, grid):
+    """KV heads that an attention workgroup takes together, by the library's rule
+    (attention_layout in attention_split.h)."""
+    tile = 8192 // row_bytes
+    hw = 1
+    if sum((p + tile) // tile for p in plen) * n_kv_heads > 8192 // (tile * 4) * 8 * grid:
+        hw = min(8, n_kv_heads)
+    while hw < 8 and hw < n_kv_heads and len(plen) * n_kv_heads // hw > grid:
+        hw *= 2
+    return hw
 
 
 def metadata_bytes(w, W, K, attended, algo_bytes, traffic, roofline):
     """Bytes the timed steps move besides the K/V rows of attended tokens and
     the logits (the algorithmic bytes), from the kernels' access pattern:
-    index lists (read by attention, written by compaction), freeze state (an
-    upper bound: count read and write plus U write for every attended token),
-    the compaction's scan of U over every position, q, out and the appended row
-    of every (layer, sequence), the split-K partials (an upper bound: one slot
-    per CU plus one per sequence, written and read by attention) and one relevance
-    plane (written by attention, read by the verdicts; short prompts and the
-    softmax reading keep more).  The attention kernel's measured counter excess
-    is given beside it."""
+    index lists (read by attention once per group of KV heads that a workgroup
+    takes together and by the verdicts, written by compaction), the relevance
+    planes (one per such group, or one per query head with the softmax reading;
+    written by attention, read by the verdicts), the score flags written, the
+    compaction's scan of U, counts and flags over every position, freeze state
+    (an upper bound: count and U written for every attended token), q, out and
+    the appended row of every (layer, sequence), and the split-K partials (an
+    upper bound: a slot of the group's query heads per CU and pair, written and
+    read).  The attention kernel's measured counter excess is given beside it."""
     import torch
     L, B, Hq, D = w.n_layers, w.batch, w.n_q_heads, w.head_dim
     esz = 2 if w.dtype == "bf16" else 4
     positions = L * sum(p + t for p in w.prefill for t in range(W + 1, W + K + 1))   # n_t, summed
     cus = torch.cuda.get_device_properties(0).multi_processor_count
+    Hkv = w.n_kv_heads
+    hw = heads_together(w.prefill, Hkv, D * esz, cus)
+    groups = Hkv // hw
     parts = {
-        "index_lists": 8 * attended,
-        "freeze_state_upper_bound": 12 * attended,
-        "compaction_scan": 4 * positions,
+        "index_lists": 4 * (groups + 2) * attended,
+        "relevance_planes": 8 * (groups if w.relevance == "abs" else Hq) * attended,
+        "score_flags": attended,
+        "freeze_state_upper_bound": 8 * attended,
+        "compaction_scan": 9 * positions,
         "q_out_append": K * L * B * (Hq * D * esz + Hq * D * 4 + w.kv_bytes_per_token()),
-        "split_partials": 2 * K * L * (cus + B) * Hq * (D + 2) * 4,
-        "relevance_plane": 8 * attended,
+        "split_partials_upper_bound": 2 * K * L * (cus * hw * (Hq // Hkv) + B * Hq) * (D + 2) * 4,
     }
     total = sum(parts.values())
     out = {"bytes_timed_steps": parts, "total": total, "fraction_of_algorithmic": total / algo_bytes}

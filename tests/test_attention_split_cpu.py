@@ -140,3 +140,13 @@ def test_forms_of_the_gpu_cases(lib, name):
     hw, _ = _heads(lib, [x - 1 for x in n], hkv, row)
     aligned, _, _ = _check(lib, n, hkv, hw, lib.split_tile(row))
     assert (hw, bool(aligned)) == (want_hw, want_aligned)
+
+
+def test_the_benchmarks_copy_of_the_rule(lib):
+    """bench.py states the relevance and list bytes from its own copy of the rule."""
+    import bench
+    rng = random.Random(11)
+    for _ in range(500):
+        hkv, row = rng.choice([(1, 128), (2, 256), (8, 256), (8, 512), (32, 256), (32, 128)])
+        plen = [rng.randint(0, int(2 ** rng.uniform(0, 16))) for _ in range(rng.choice([1, 2, 8, 33, 64, 100, 500]))]
+        assert bench.heads_together(plen, hkv, row, GRID) == _heads(lib, plen, hkv, row)[0]
