@@ -173,10 +173,12 @@ asrkf_status asrkf_init(const asrkf_config* cfg, asrkf_ctx** out);
 
 /* Copy the prompt KV of one (layer, sequence) into the cache (Sec. 3.1: the
  * pairs (K_j, V_j) of every previous token).  k, v: device,
- * [n_tokens][n_kv_heads][head_dim] of cfg.dtype.  Every layer of a sequence
- * must be given the same n_tokens (1 .. max_ctx-1); a sequence never
- * prefilled starts empty.  Only before the first decode step (else ESTATE).
- * Asynchronous. */
+ * [n_tokens][n_kv_heads][head_dim] of cfg.dtype (EINVAL where that reaches
+ * past the end of an allocation; memory that a kernel on this device cannot
+ * read, such as host memory, goes through the runtime's copies).  Every layer
+ * of a sequence must be given the same n_tokens (1 .. max_ctx-1); a sequence
+ * never prefilled starts empty.  Only before the first decode step (else
+ * ESTATE).  Asynchronous. */
 asrkf_status asrkf_prefill(asrkf_ctx* ctx, int32_t layer, int32_t seq,
                            const void* k, const void* v, int32_t n_tokens, void* stream);
 

@@ -184,6 +184,7 @@ struct PrefillArgs {
     char* vdst;
     int32_t* plen;            // the sequence's prompt length, written when set_plen
     int32_t n, Hkv, row_bytes, pool_rows, set_plen;
+    int32_t rows;             // rows that the kernel copies: n, or 0 (only the length is set)
 };
 
 // Row copies between the device cache and the host store (spill mode).

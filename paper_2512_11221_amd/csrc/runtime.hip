@@ -357,6 +357,25 @@ hipError_t clear_state(asrkf_ctx* ctx, hipStream_t s) {
     return launch_clear(a, s);
 }
 
+// Whether a kernel on the context's device may read p[0 .. bytes): memory of that
+// device (inside says whether the range lies in p's allocation).  Host memory,
+// another device's, and pointers that the runtime does not know are left to the
+// runtime's own copies, which take or refuse them.
+bool kernel_readable(const asrkf_ctx* ctx, const void* p, size_t bytes, bool* inside) {
+    *inside = true;
+    hipPointerAttribute_t attr{};
+    hipDeviceptr_t base = nullptr;
+    size_t size = 0;
+    if (hipPointerGetAttributes(&attr, p) != hipSuccess || attr.type != hipMemoryTypeDevice ||
+        attr.device != ctx->device ||
+        hipMemGetAddressRange(&base, &size, const_cast<void*>(p)) != hipSuccess) {
+        (void)hipGetLastError();
+        return false;
+    }
+    *inside = static_cast<const char*>(p) + bytes <= static_cast<const char*>(base) + size;
+    return true;
+}
+
 void mark_queued(asrkf_ctx* ctx, hipStream_t s, bool capture) {
     ctx->last_stream = s;
     ctx->queued = true;
@@ -589,6 +608,11 @@ asrkf_status asrkf_prefill(asrkf_ctx* ctx, int32_t layer, int32_t seq, const voi
         return fail(ASRKF_EINVAL, "sequence %d was prefilled with %d tokens in another layer",
                     seq, ctx->plen_host[seq]);
     hipStream_t s = static_cast<hipStream_t>(stream);
+    bool inside_k, inside_v;
+    const size_t bytes = (size_t)n_tokens * ctx->row_bytes;
+    const bool direct_k = kernel_readable(ctx, k, bytes, &inside_k), direct_v = kernel_readable(ctx, v, bytes, &inside_v);
+    if (!inside_k || !inside_v)
+        return fail(ASRKF_EINVAL, "%s is smaller than %d tokens (%zu bytes)", inside_k ? "v" : "k", n_tokens, bytes);
     HIP_OK(ctx, follow_last_stream(ctx, s));
     const size_t off = ((size_t)layer * c.batch + seq) * ctx->pool_rows * ctx->row_bytes;
     PrefillArgs p{};
@@ -602,6 +626,18 @@ asrkf_status asrkf_prefill(asrkf_ctx* ctx, int32_t layer, int32_t seq, const voi
     p.row_bytes = (int32_t)(c.head_dim * ctx->esz);
     p.pool_rows = ctx->pool_rows;
     p.set_plen = ctx->prefilled[seq] ? 0 : 1;
+    p.rows = n_tokens;
+    if (!direct_k || !direct_v) {
+        // memory that the kernel cannot read: a strided copy per KV head
+        p.rows = 0;
+        for (int g = 0; g < c.n_kv_heads; ++g) {
+            const size_t src = (size_t)g * p.row_bytes, dst = (size_t)g * ctx->pool_rows * p.row_bytes;
+            HIP_OK(ctx, hipMemcpy2DAsync(p.kdst + dst, p.row_bytes, p.k + src, ctx->row_bytes, p.row_bytes, n_tokens,
+                                         hipMemcpyDefault, s));
+            HIP_OK(ctx, hipMemcpy2DAsync(p.vdst + dst, p.row_bytes, p.v + src, ctx->row_bytes, p.row_bytes, n_tokens,
+                                         hipMemcpyDefault, s));
+        }
+    }
     HIP_OK(ctx, launch_prefill(p, s));
     ctx->prefilled[seq] = 1;
     ctx->plen_host[seq] = n_tokens;

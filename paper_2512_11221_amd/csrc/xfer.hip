@@ -62,7 +62,7 @@ prefill_kernel(PrefillArgs a) {
     T* dst = reinterpret_cast<T*>(second ? a.vdst : a.kdst);
     const unsigned per_row = a.row_bytes / sizeof(T);     // pieces per head row: a power of two
     const unsigned row_shift = __ffs((int)per_row) - 1, head_shift = __ffs(a.Hkv) - 1;
-    const unsigned total = (unsigned)a.n * a.Hkv * per_row;    // below 2^31: a sequence's rows are
+    const unsigned total = (unsigned)a.rows * a.Hkv * per_row; // below 2^31: a sequence's rows are
     const unsigned stride = half * kCopyThreads * kCopyUnroll;
     if (a.set_plen && blockIdx.x == 0 && threadIdx.x == 0) *a.plen = a.n;
     for (unsigned i0 = (second ? blockIdx.x - half : blockIdx.x) * kCopyThreads * kCopyUnroll + threadIdx.x;
@@ -98,9 +98,10 @@ hipError_t launch_prefill(const PrefillArgs& a, hipStream_t s) {
     if (a.n < 1 || a.row_bytes % 16) return hipErrorInvalidValue;
     const uintptr_t low = reinterpret_cast<uintptr_t>(a.k) | reinterpret_cast<uintptr_t>(a.v);
     const int piece = (low & 15) == 0 ? 16 : (low & 3) == 0 ? 4 : (low & 1) == 0 ? 2 : 1;
-    const size_t pieces = (size_t)a.n * a.Hkv * a.row_bytes / piece;
+    const size_t pieces = (size_t)a.rows * a.Hkv * a.row_bytes / piece;
     constexpr size_t kPerBlock = kCopyThreads * kCopyUnroll;
     size_t half = (pieces + kPerBlock - 1) / kPerBlock;
+    if (half < 1) half = 1;
     if (half > 1024) half = 1024;                 // 8 workgroups per CU in all
     const dim3 grid((unsigned)(2 * half)), block(kCopyThreads);
     typedef unsigned u4 __attribute__((ext_vector_type(4)));

@@ -78,6 +78,9 @@ int main(void) {
     CHECK(hipMalloc((void**)&dq, (size_t)B * HQ * D * sizeof(float)) == hipSuccess);
     CHECK(hipMalloc((void**)&dout, (size_t)B * HQ * D * sizeof(float)) == hipSuccess);
     const int plen[B] = {P0, P1};
+    /* a prompt that reaches past the end of its allocation is refused, with nothing done */
+    CHECK(asrkf_prefill(ctx, 0, 0, (char*)dk + (CAP - P0 / 2) * row, dv, P0, NULL) == ASRKF_EINVAL);
+    CHECK(asrkf_prefill(ctx, 0, 0, dk, (char*)dv + (CAP - P0 / 2) * row, P0, NULL) == ASRKF_EINVAL);
     for (int b = 0; b < B; ++b) {
         if (!plen[b]) continue;
         CHECK(hipMemcpy(dk, kall[b], plen[b] * row, hipMemcpyHostToDevice) == hipSuccess);

@@ -279,3 +279,37 @@ def test_reset_context_runs_like_a_fresh_one(spill):
     o = H.run_oracle(w, H.Inputs(w), inst)
     for key in inst:
         H.compare_instance(fresh[key], o[key])
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("where", ["pageable", "pinned", "k only"])
+def test_prompts_outside_the_devices_memory(gpu, where, dtype):
+    """Prompts in host memory, ordinary or pinned, or one tensor of the two, land in
+    the cache like those on the device: the outputs are the same bit for bit."""
+    torch = gpu
+    import paper_2512_11221_amd as A
+    dt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    n, Hkv, D = 201, 4, 64
+    g = torch.Generator(device="cuda").manual_seed(43)
+    k, v = (torch.randn((n, Hkv, D), generator=g, device="cuda", dtype=dt) for _ in range(2))
+    q = torch.randn((2, 8, D), generator=g, device="cuda", dtype=dt)
+    new = torch.randn((2, 2, Hkv, D), generator=g, device="cuda", dtype=dt)
+    host = [x.cpu().pin_memory() if where == "pinned" else x.cpu() for x in (k, v)]
+    if where == "k only":
+        host[1] = v
+    outs = []
+    for kk, vv in ((k, v), host):
+        ctx = A.asrkf_init(A.make_config(2, 2, 8, Hkv, D, n + 3, 16, 0.5, 2.0, 16, dtype=dtype))
+        try:
+            out = torch.empty((2, 2, 8, D), device="cuda")
+            for l in range(2):
+                A.asrkf_prefill(ctx, l, 1, kk, vv, n)
+            for _ in range(2):
+                for l in range(2):
+                    A.asrkf_decode_step(ctx, l, q, new[0], new[1], out[l])
+                A.asrkf_restore(ctx, None, A.NONE)
+            assert A.asrkf_stats(ctx)["total_positions"] == 2 * (n + 4)
+            outs.append(out.cpu())
+        finally:
+            A.asrkf_destroy(ctx)
+    assert torch.equal(outs[0], outs[1])
